@@ -115,7 +115,7 @@ __global__ __launch_bounds__(256, ((sizeof(T) == 4 && TWM == 1 && UNI && !M2) ||
     int64_t rec = 0;          // record slot of the active half line
     Lane<T> L{};
     LaneConst<T> K{};
-    K.max_steps = tp.max_steps;
+    K.max_steps = (uint32_t)(tp.max_steps < 0xfffffffell ? tp.max_steps : 0xfffffffell);
     const void *nodes = nullptr;
     if (UNI) {
         const TraceJob &J0 = jobs[0];

@@ -36,20 +36,26 @@ template <typename T, typename S, bool TW, bool WIDE = TW>
 __device__ __forceinline__ void load_cell(const void *nodes, int nx, int ny, int cx, int cy,
                                           int cz, T cb[3][8], T cj[3][8])
 {
-    const FQ_GLOBAL typename V4<S>::t *A = gptr((const typename V4<S>::t *)nodes);
-    const int64_t sx = 1, sy = nx, sz = (int64_t)nx * ny;
-    const int64_t base = (int64_t)cz * sz + (int64_t)cy * sy + cx;
+    using V = typename V4<S>::t;
+    constexpr unsigned kRec = (WIDE ? 2 : 1) * sizeof(V);
+    // one 64-bit address (c, n < 2^16: the row index takes a 24-bit multiply), the other
+    // three corner rows at uniform distances from it, the x neighbour at a fixed one
+    const unsigned row = __umul24((unsigned)cz, (unsigned)ny) + (unsigned)cy;
+    const FQ_GLOBAL char *A = gptr((const char *)nodes) +
+                              ((uint64_t)row * (unsigned)nx + (unsigned)cx) * kRec;
+    const int64_t sy = (int64_t)nx * kRec, sz = (int64_t)ny * sy;
     T f[6][8];
 #pragma unroll
     for (int q = 0; q < 8; q++) {
-        const int64_t o = base + ((q & 1) ? sx : 0) + ((q & 2) ? sy : 0) + ((q & 4) ? sz : 0);
-        const typename V4<S>::t a = A[WIDE ? 2 * o : o];
+        const FQ_GLOBAL V *r = (const FQ_GLOBAL V *)(A + ((q & 2) ? sy : 0) + ((q & 4) ? sz : 0) +
+                                                     ((q & 1) ? kRec : 0));
+        const V a = r[0];
         f[0][q] = (T)a.x;
         f[1][q] = (T)a.y;
         f[2][q] = (T)a.z;
         f[3][q] = (T)a.w;
         if (TW) {
-            const typename V4<S>::t c = A[2 * o + 1];
+            const V c = r[1];
             f[4][q] = (T)c.x;
             f[5][q] = (T)c.y;
         }
