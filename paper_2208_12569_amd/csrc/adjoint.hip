@@ -496,7 +496,6 @@ struct Capture {
     int *axis;
     double *H;
     int *clamp;
-    __device__ __forceinline__ void operator()(int) const {}
     template <typename T> __device__ __forceinline__ void accepted(int a, T h, int cl) const
     {
         *axis = a;

@@ -27,6 +27,9 @@ struct Carve {
     }
 };
 
+// lanes of one wave per SIMD on every CU
+constexpr int64_t kLanes = 256 * 4 * 64;
+
 enum SpecKind { SPEC_LIST, SPEC_PLANE, SPEC_VOXELS, SPEC_CYL };
 
 struct Spec {
@@ -450,6 +453,13 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
                                        (uint32_t *)(ws + w.rot_count), w.nlines, stream));
         }
     }
+    // The tiles are put in order only where some lines have to wait for others to end:
+    // a call whose lines all start at once (at most 64 per SIMD, which every tracer grid
+    // holds) gains nothing from it.
+    int64_t live_lines = 0;
+    for (int i = 0; i < ns; i++)
+        live_lines += W[i].nlines * (specs[i].kind == SPEC_PLANE && plane_on_face(specs[i].pl, *specs[i].f) ? 1 : 2);
+    const bool ordered = live_lines > kLanes || P.waves_per_cu > 0;
     // job table
     std::vector<TraceJob> jobs(njobs);
     int64_t items = 0;
@@ -525,12 +535,12 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
         }
         J.nitems = tv;
         set_job_constants(J);
-        if (s.kind == SPEC_PLANE) {
+        if (s.kind == SPEC_PLANE && ordered) {
             J.tile_order = (const int32_t *)(ws + w.tile_order);
             if (fwd)
                 FQ_TRY(launch_tile_order(J, P.precision, P.want_tw, (int32_t *)(ws + w.tile_bucket), (uint32_t *)(ws + w.tile_counts),
                                          (int32_t *)(ws + w.tile_order), stream));
-        } else if (s.kind == SPEC_VOXELS) {
+        } else if (s.kind == SPEC_VOXELS && ordered) {
             J.tile_order = (const int32_t *)(ws + w.tile_order);
             if (fwd)
                 FQ_TRY(launch_voxel_order(J, P.precision, P.want_tw, (int32_t *)(ws + w.tile_bucket),
@@ -775,6 +785,8 @@ void set_job_constants(TraceJob &J)
     for (int a = 0; a < 3; a++) J.inv_spacing[a] = 1.0 / J.spacing[a];
     J.inv_t0 = 1.0 / (double)J.tiles[0];
     J.inv_t1 = 1.0 / (double)J.tiles[1];
+    J.inv_d0 = 1.0 / (double)J.dims[0];
+    J.inv_d1 = 1.0 / (double)J.dims[1];
 }
 
 void plane_normal(const fq_plane &p, double n[3])

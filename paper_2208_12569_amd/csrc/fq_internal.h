@@ -88,6 +88,7 @@ struct TraceJob {
     double dref;         // reference length (smallest spacing; uniform grids)
     double inv_spacing[3];
     double inv_t0, inv_t1; // 1 / tiles[0], 1 / tiles[1] (tile decode)
+    double inv_d0, inv_d1; // 1 / dims[0], 1 / dims[1] (line decode)
 };
 
 // One half line to trace again (FP64 pass).

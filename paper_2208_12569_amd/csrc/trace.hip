@@ -107,6 +107,11 @@ __global__ __launch_bounds__(256, ((sizeof(T) == 4 && TWM == 1 && UNI && !M2) ||
         total = *tp.total_dev;  // with the rotated-S0 jobs, sized on the device
     }
 
+    // Few items: the waves that have none to take end at once. Waves are ranked across the
+    // blocks first, so that those that stay sit on different CUs: the four of a block
+    // would share one CU's gather path (a 17 000-line FP64 pass is a fifth slower so).
+    if ((int64_t)((threadIdx.x >> 6) * gridDim.x + blockIdx.x) * 64 >= total) return;
+
     // lane state
     int jb = -1;              // job of the active half line, -1 = idle
     bool exhausted = false;
@@ -191,12 +196,12 @@ __global__ __launch_bounds__(256, ((sizeof(T) == 4 && TWM == 1 && UNI && !M2) ||
                     if (!xsplit || xtried >= 8) exhausted = true;
                 } else {
                     int j = 0;
-                    int64_t line;
+                    LineAt at;
                     bool forward;
                     if (tp.list) {
                         const FixEntry e = gptr(tp.list)[tp.list_rev ? tp.list_cap - 1 - it : it];
                         j = UNI ? 0 : e.job;
-                        line = e.line;
+                        at = line_at(jobs[j], e.line);
                         forward = e.half != 0;
                     } else {
                         // the job whose range of items holds it (the ranges need not
@@ -213,16 +218,16 @@ __global__ __launch_bounds__(256, ((sizeof(T) == 4 && TWM == 1 && UNI && !M2) ||
                             // the forward and backward halves of a tile follow each
                             // other, so long lines of either direction start early
                             forward = ((local >> 6) & 1) == 0;
-                            line = line_of_item(J, ((local >> 7) << 6) | (local & 63));
+                            at = line_of_item(J, ((local >> 7) << 6) | (local & 63));
                         } else {
                             forward = local < nit;
-                            line = line_of_item(J, forward ? local : local - nit);
+                            at = line_of_item(J, forward ? local : local - nit);
                         }
                     }
-                    if (line >= 0) {
+                    if (at.line >= 0) {
                         const TraceJob &J = jobs[j];
                         double r[3], nrm[3];
-                        seed_of_line<CYLK>(J, line, r, nrm);
+                        seed_of_line<CYLK>(J, at, r, nrm);
                         jb = j;
                         if (!UNI) {
                             nodes = J.nodes;
@@ -242,7 +247,7 @@ __global__ __launch_bounds__(256, ((sizeof(T) == 4 && TWM == 1 && UNI && !M2) ||
                                 K.twk = (T)(dref_s * (0.25 / M_PI));
                             }
                         }
-                        rec = (forward ? J.nlines : 0) + line;
+                        rec = (forward ? J.nlines : 0) + at.line;
                         L.sgn = forward ? T(1) : T(-1);
                         L.tw = 0.0;
                         L.len = 0.0;
@@ -467,7 +472,7 @@ __global__ __launch_bounds__(256, ((sizeof(T) == 4 && TWM == 1 && UNI && !M2) ||
                 // half line ends exactly at its seed, not at the seed's position as
                 // rounded into local coordinates of the compute type
                 double r[3], nrm[3];
-                seed_of_line<CYLK>(J, rec >= J.nlines ? rec - J.nlines : rec, r, nrm);
+                seed_of_line<CYLK>(J, line_at(J, rec >= J.nlines ? rec - J.nlines : rec), r, nrm);
                 e0 = r[0];
                 e1 = r[1];
                 e2 = r[2];
@@ -556,7 +561,7 @@ __global__ void graze_kernel(const TraceJob *__restrict__ jobs, int job, double 
         bool seed_graze = false;
         if (seed_check && J.kind != SEED_ROTATED) {
             double r[3], nrm[3], B[3];
-            seed_of_line(J, l, r, nrm);
+            seed_of_line(J, line_at(J, l), r, nrm);
             interp64(J.planes, r, B);
             const double bm = sqrt(B[0] * B[0] + B[1] * B[1] + B[2] * B[2]);
             const double bn = B[0] * nrm[0] + B[1] * nrm[1] + B[2] * nrm[2];
@@ -1009,19 +1014,49 @@ hipError_t launch_bucket_order(int64_t n, int32_t *key, uint32_t *counts, int32_
     return hipGetLastError();
 }
 
+namespace {
+// The kernel a launch_trace call picks (no tape) and the blocks per CU its grid has.
+const void *pick_kernel(int prec, int store, int twm, const TraceParams &tp)
+{
+    const bool f64 = prec == FQ_PREC_F64, s64 = store == FQ_DT_F64;
+    // stretched grids take the multi-job kernels, which carry their per-cell scales
+    const bool uni = tp.njobs == 1 && !tp.dynamic_last && !tp.stretched && !tp.cyl;
+    const int sch = tp.scheme, mt = tp.method;
+    if (!f64) return uni ? kernel_of<float, float, true>(twm, sch, mt) : kernel_of<float, float, false>(twm, sch, mt);
+    if (s64) return uni ? kernel_of<double, double, true>(twm, sch, mt) : kernel_of<double, double, false>(twm, sch, mt);
+    return uni ? kernel_of<double, float, true>(twm, sch, mt) : kernel_of<double, float, false>(twm, sch, mt);
+}
+
+int cu_count()
+{
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
+    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) ncu = 0;
+    return ncu > 0 ? ncu : 256;
+}
+
+int blocks_per_cu(const void *fn, int block, int waves_per_cu)
+{
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, block, 0) != hipSuccess) per_cu = 0;
+    if (per_cu <= 0) per_cu = 1;
+    if (waves_per_cu > 0) {
+        const int want = (waves_per_cu * 64 + block - 1) / block;
+        if (want < per_cu) per_cu = want;
+        if (per_cu < 1) per_cu = 1;
+    }
+    return per_cu;
+}
+}  // namespace
+
 hipError_t launch_trace(int prec, int store, int twm, const TraceJob *jobs_dev,
                         const TraceParams &tp, unsigned long long *counter, int block,
                         int waves_per_cu, hipStream_t s)
 {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-    int ncu = 0;
-    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) ncu = 0;
-    if (ncu <= 0) ncu = 256;
+    const int ncu = cu_count();
     if (block <= 0) block = 256;
     const bool f64 = prec == FQ_PREC_F64, s64 = store == FQ_DT_F64;
     if (!f64 && s64) return hipErrorInvalidValue;  // FP32 arithmetic reads FP32 records only
-    // stretched grids take the multi-job kernels, which carry their per-cell scales
     const bool uni = tp.njobs == 1 && !tp.dynamic_last && !tp.stretched && !tp.cyl;
     if (tp.scheme < SCH_RKF45 || tp.scheme > SCH_RK4_38) return hipErrorInvalidValue;
     if (tp.tape) {
@@ -1044,21 +1079,9 @@ hipError_t launch_trace(int prec, int store, int twm, const TraceJob *jobs_dev,
         }
         return hipGetLastError();
     }
-    const void *fn;
-    const int sch = tp.scheme, mt = tp.method;
-    if (mt == FQ_METHOD_II && (sch != SCH_RKF45 || twm == 2 || twm == 3)) return hipErrorInvalidValue;
+    if (tp.method == FQ_METHOD_II && (tp.scheme != SCH_RKF45 || twm == 2 || twm == 3)) return hipErrorInvalidValue;
     if (twm == 3 && !f64) return hipErrorInvalidValue;
-    if (!f64) fn = uni ? kernel_of<float, float, true>(twm, sch, mt) : kernel_of<float, float, false>(twm, sch, mt);
-    else if (s64) fn = uni ? kernel_of<double, double, true>(twm, sch, mt) : kernel_of<double, double, false>(twm, sch, mt);
-    else fn = uni ? kernel_of<double, float, true>(twm, sch, mt) : kernel_of<double, float, false>(twm, sch, mt);
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, block, 0) != hipSuccess) per_cu = 0;
-    if (per_cu <= 0) per_cu = 1;
-    if (waves_per_cu > 0) {
-        int want = (waves_per_cu * 64 + block - 1) / block;
-        if (want < per_cu) per_cu = want;
-        if (per_cu < 1) per_cu = 1;
-    }
+    const int per_cu = blocks_per_cu(pick_kernel(prec, store, twm, tp), block, waves_per_cu);
     dim3 grid((unsigned)(per_cu * ncu)), blk((unsigned)block);
     if (!f64) {
         if (uni) launch_ts<float, float, true, false>(twm, grid, blk, s, jobs_dev, tp, counter);

@@ -361,7 +361,6 @@ __host__ __device__ __forceinline__ void lane_iterate(Lane<T> &L, const T cb[3][
     // not heading to that face yet: approach it with a plain step
     const bool noland = land & (wrong_way | !(fabs(g0) > N::gmin) | (H == T(0)));
     const bool step = live & !cross & !noland;
-
     const bool hneg = !(H >= T(0));
     const T ig0 = N::rcp(g0);
 

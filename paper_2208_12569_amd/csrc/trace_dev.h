@@ -85,11 +85,55 @@ __device__ __forceinline__ int64_t live_lines(const TraceJob &J)
     return cnt < J.nlines ? cnt : J.nlines;
 }
 
+// floor(n / d) and the remainder for 0 <= n < 2^34, d > 0, with a precomputed 1/d: one FP64
+// multiply (its quotient is off by at most one) and an exact correction; 32-bit
+// integers where n has that size, several times fewer instructions than a 64-bit
+// division.
+__device__ __forceinline__ int64_t fdiv(int64_t n, int64_t d, double inv_d, int64_t &rem)
+{
+    if (n <= INT32_MAX && d <= INT32_MAX) {
+        const int32_t n32 = (int32_t)n, d32 = (int32_t)d;
+        int32_t q = (int32_t)((double)n32 * inv_d);
+        int32_t r = n32 - q * d32;
+        if (r < 0) q--, r += d32;
+        else if (r >= d32) q++, r -= d32;
+        rem = r;
+        return q;
+    }
+    int64_t q = (int64_t)((double)n * inv_d);
+    int64_t r = n - q * d;
+    if (r < 0) q--, r += d;
+    else if (r >= d) q++, r -= d;
+    rem = r;
+    return q;
+}
+
+// A line and, where its job's seeds form a grid, its seed's indices there.
+struct LineAt {
+    int64_t line;
+    int64_t i, j, k;
+};
+
+__device__ __forceinline__ bool seeds_on_grid(const TraceJob &J)
+{
+    return J.kind == SEED_PLANE || J.kind == SEED_VOXELS || J.kind == SEED_CYL;
+}
+
+__device__ __forceinline__ LineAt line_at(const TraceJob &J, int64_t line)
+{
+    LineAt l{line, 0, 0, 0};
+    if (seeds_on_grid(J)) {
+        const int64_t row = fdiv(line, J.dims[0], J.inv_d0, l.i);
+        l.k = fdiv(row, J.dims[1], J.inv_d1, l.j);
+    }
+    return l;
+}
+
 // Seed position of a line and the S0 normal used for the Eq. step / Eq. tol scaling
 // (zero for rotated S0, whose normal is along B). CYL: cylinder jobs may occur (the
 // kernels that never see them leave out their trigonometry).
 template <bool CYL = true>
-__device__ __forceinline__ void seed_of_line(const TraceJob &J, int64_t line, double r[3],
+__device__ __forceinline__ void seed_of_line(const TraceJob &J, const LineAt &l, double r[3],
                                              double nrm[3])
 {
     nrm[0] = J.normal[0];
@@ -97,34 +141,30 @@ __device__ __forceinline__ void seed_of_line(const TraceJob &J, int64_t line, do
     nrm[2] = J.normal[2];
     if (J.kind == SEED_LIST) {
         const FQ_GLOBAL double *sd = gptr(J.seeds);
-        r[0] = sd[3 * line + 0];
-        r[1] = sd[3 * line + 1];
-        r[2] = sd[3 * line + 2];
+        r[0] = sd[3 * l.line + 0];
+        r[1] = sd[3 * l.line + 1];
+        r[2] = sd[3 * l.line + 2];
     } else if (J.kind == SEED_ROTATED) {
-        const FQ_GLOBAL RotEntry &e = gptr(J.rot)[line >> 2];
-        const int which = (int)(line & 3);
+        const FQ_GLOBAL RotEntry &e = gptr(J.rot)[l.line >> 2];
+        const int which = (int)(l.line & 3);
         const double *d = (which < 2) ? e.U : e.V;
         const double s = (which & 1) ? J.rot_delta : -J.rot_delta;
         for (int a = 0; a < 3; a++) r[a] = e.r0[a] + s * d[a];
         nrm[0] = nrm[1] = nrm[2] = 0.0;
     } else if (CYL && J.kind == SEED_CYL) {
         // a seed on the cylinder; the S0 normal is its outward normal there
-        const int64_t i = line % J.dims[0], j = line / J.dims[0];
-        const double t = J.s_origin[0] + (double)i * J.s_a[0];
+        const double t = J.s_origin[0] + (double)l.i * J.s_a[0];
         const double ct = cos(t), st = sin(t);
         r[0] = J.cyl[0] + J.cyl[2] * ct;
         r[1] = J.cyl[1] + J.cyl[2] * st;
-        r[2] = J.s_origin[1] + (double)j * J.s_b[1];
+        r[2] = J.s_origin[1] + (double)l.j * J.s_b[1];
         nrm[0] = ct;
         nrm[1] = st;
         nrm[2] = 0.0;
     } else {
-        const int64_t i = line % J.dims[0];
-        const int64_t j = (line / J.dims[0]) % J.dims[1];
-        const int64_t k = line / (J.dims[0] * J.dims[1]);
         for (int a = 0; a < 3; a++)
-            r[a] = J.s_origin[a] + (double)i * J.s_a[a] + (double)j * J.s_b[a] +
-                   (double)k * J.s_c[a];
+            r[a] = J.s_origin[a] + (double)l.i * J.s_a[a] + (double)l.j * J.s_b[a] +
+                   (double)l.k * J.s_c[a];
     }
 }
 
@@ -162,47 +202,34 @@ __device__ __forceinline__ double grid_pos(const TraceJob &J, int a, int c, doub
     return xg[c] + p * (xg[c + 1] - xg[c]);
 }
 
-// floor(n / d) for 0 <= n < 2^31 with a precomputed 1/d (one FP64 multiply and
-// an exact integer correction)
-__device__ __forceinline__ int64_t fdiv(int64_t n, int64_t d, double inv_d, int64_t &rem)
-{
-    int64_t q = (int64_t)((double)n * inv_d);
-    int64_t r = n - q * d;
-    if (r < 0) {
-        q--;
-        r += d;
-    } else if (r >= d) {
-        q++;
-        r -= d;
-    }
-    rem = r;
-    return q;
-}
-
 // Line of queue item t of a job; -1 for tile holes. Plane seeds come in 8x8 tiles,
 // voxels in 4x4x4 tiles (64 neighbouring seeds per wave), lists in order. Tiles are
 // taken in the job's tile order when it has one.
-__device__ __forceinline__ int64_t line_of_item(const TraceJob &J, int64_t t)
+__device__ __forceinline__ LineAt line_of_item(const TraceJob &J, int64_t t)
 {
-    if (J.kind == SEED_LIST || J.kind == SEED_ROTATED) return t < live_lines(J) ? t : -1;
+    LineAt l{-1, 0, 0, 0};
+    if (J.kind == SEED_LIST || J.kind == SEED_ROTATED) {
+        if (t < live_lines(J)) l.line = t;
+        return l;
+    }
     int64_t ti = t >> 6;
     if (J.tile_order) ti = gptr(J.tile_order)[ti];
     const int w = (int)(t & 63);
-    int64_t r0, i, j, k;
+    int64_t r0;
     const int64_t q0 = fdiv(ti, J.tiles[0], J.inv_t0, r0);
     if (J.kind == SEED_PLANE || J.kind == SEED_CYL) {
-        i = r0 * 8 + (w & 7);
-        j = q0 * 8 + (w >> 3);
-        k = 0;
+        l.i = r0 * 8 + (w & 7);
+        l.j = q0 * 8 + (w >> 3);
     } else {
         int64_t r1;
         const int64_t q1 = fdiv(q0, J.tiles[1], J.inv_t1, r1);
-        i = r0 * 4 + (w & 3);
-        j = r1 * 4 + ((w >> 2) & 3);
-        k = q1 * 4 + (w >> 4);
+        l.i = r0 * 4 + (w & 3);
+        l.j = r1 * 4 + ((w >> 2) & 3);
+        l.k = q1 * 4 + (w >> 4);
     }
-    if (i >= J.dims[0] || j >= J.dims[1] || k >= J.dims[2]) return -1;
-    return (k * J.dims[1] + j) * J.dims[0] + i;
+    if (l.i < J.dims[0] && l.j < J.dims[1] && l.k < J.dims[2])
+        l.line = (l.k * J.dims[1] + l.j) * J.dims[0] + l.i;
+    return l;
 }
 
 }  // namespace dev
