@@ -76,24 +76,39 @@ template <typename T> constexpr int refill_min() { return sizeof(T) == 4 ? 24 : 
 
 // TWM: 0 = no twist (narrow records), 1 = twist, 2 = positions only on wide records
 // (the FP64 re-trace, which keeps the twist of the first pass); 3 = as 2, held to
-// three waves per SIMD (168 VGPRs, about 100 bytes of spills per lane) for calls
+// three waves per SIMD (168 VGPRs, 52-64 bytes of spills per lane) for calls
 // that share the GPU with other maps in flight: its waves then leave room for theirs.
-// The FP32 single-job kernel is held to 168 VGPRs so that three waves fit per SIMD
-// (the latency of cell fetches is then hidden by more waves), and the FP32 Method II
-// kernels to two waves per SIMD (a few bytes of spills; at one wave their lone
-// waves took 40% longer than the two-wave form).
 // SCH: the integration scheme (Scheme in trace_core.h), the adjoint's forward pass
 // (TAPE) included. M2: Method II, the tangent vectors U, V ride along (their
-// end values go to the records' uv array).
-template <typename T, typename S, int TWM, bool UNI, bool TAPE, int SCH = SCH_RKF45, bool M2 = false>
-__global__ __launch_bounds__(256, ((sizeof(T) == 4 && TWM == 1 && UNI && !M2) || TWM == 3) ? 3 : ((sizeof(T) == 4 && M2) ? 2 : 1)) void trace_kernel(const TraceJob *__restrict__ jobs,
+// end values go to the records' uv array). CYL: jobs may run inside a cylinder.
+//
+// Waves per SIMD each kernel's registers are held to. With the twist summed stage by
+// stage the FP32 kernels need 142-160 VGPRs and the FP64 ones 245-252, without spills:
+// three waves and two (168 and 256). More waves fill the issue slots that a wave leaves
+// while it waits for its cell fetches (29% of an FP64 wave's time, 32% of a multi-job
+// FP32 wave's): a 1024 x 1024 FP64 map 7.36 -> 5.57 ms (one wave -> two), a 256x256x128
+// voxel map 195 -> 187 ms and a batch of 8 cubes 35.7 -> 32.8 ms (two -> three; the
+// single-job FP32 kernel had three). Four waves of FP32 (128 VGPRs, spills) are slower
+// than three (4.88 -> 5.00 ms at 1024 x 1024). Method II in FP64 stays at one wave: at
+// two it spills 680 bytes (5.4 -> 6.3 ms); its FP32 kernels (198-203 VGPRs) and the
+// cylinder's (183) run two.
+template <typename T, int TWM, bool M2, bool CYL> constexpr int waves_per_simd()
+{
+    if (sizeof(T) == 4) return M2 || CYL ? 2 : 3;
+    return M2 ? 1 : (TWM == 3 ? 3 : 2);
+}
+
+template <typename T, typename S, int TWM, bool UNI, bool TAPE, int SCH = SCH_RKF45, bool M2 = false,
+          bool CYL = false>
+__global__ __launch_bounds__(256, (waves_per_simd<T, TWM, M2, CYL>())) void trace_kernel(const TraceJob *__restrict__ jobs,
                                                     TraceParams tp,
                                                     unsigned long long *__restrict__ counter)
 {
     using N = Num<T>;
     constexpr bool TW = TWM == 1;
-    // cylindrical mapping surfaces: the multi-job Method I kernels only
-    constexpr bool CYLK = !UNI && !M2 && !TAPE;
+    // cylindrical mapping surfaces: kernels of their own, as the multi-job Method I ones
+    static_assert(!CYL || (!UNI && !M2 && !TAPE), "cylinders take multi-job Method I kernels");
+    constexpr bool CYLK = CYL;
     // stretched grids: the multi-job kernels, and the adjoint's single-job forward pass
     constexpr bool STRK = !UNI || TAPE;
     const int lane = threadIdx.x & 63;
@@ -605,57 +620,32 @@ __global__ void graze_kernel(const TraceJob *__restrict__ jobs, int job, double 
     }
 }
 
-template <typename T, typename S, bool UNI, int SCH>
+// The kernel for a twist mode, scheme, method and mapping surface.
+template <typename T, typename S, bool UNI, bool TAPE, int SCH, bool CYL>
 const void *kernel_of_s(int twm)
 {
-    if constexpr (sizeof(T) == 8)
-        if (twm == 3) return (const void *)trace_kernel<T, S, 3, UNI, false, SCH>;
-    return twm == 1 ? (const void *)trace_kernel<T, S, 1, UNI, false, SCH>
-                    : twm == 2 ? (const void *)trace_kernel<T, S, 2, UNI, false, SCH>
-                               : (const void *)trace_kernel<T, S, 0, UNI, false, SCH>;
-}
-
-template <typename T, typename S, bool UNI>
-const void *kernel_of(int twm, int sch, int method)
-{
-    if (method == FQ_METHOD_II)
-        return twm == 1 ? (const void *)trace_kernel<T, S, 1, UNI, false, SCH_RKF45, true>
-                        : (const void *)trace_kernel<T, S, 0, UNI, false, SCH_RKF45, true>;
-    return sch == SCH_RK4 ? kernel_of_s<T, S, UNI, SCH_RK4>(twm)
-                          : sch == SCH_RK4_38 ? kernel_of_s<T, S, UNI, SCH_RK4_38>(twm)
-                                              : kernel_of_s<T, S, UNI, SCH_RKF45>(twm);
-}
-
-template <typename T, typename S, bool UNI, bool TAPE, int SCH>
-void launch_tss(int twm, dim3 grid, dim3 blk, hipStream_t s, const TraceJob *jobs,
-                const TraceParams &tp, unsigned long long *counter)
-{
     if constexpr (sizeof(T) == 8 && !TAPE)
-        if (twm == 3) {
-            hipLaunchKernelGGL((trace_kernel<T, S, 3, UNI, false, SCH>), grid, blk, 0, s, jobs, tp, counter);
-            return;
-        }
-    if (twm == 1) hipLaunchKernelGGL((trace_kernel<T, S, 1, UNI, TAPE, SCH>), grid, blk, 0, s, jobs, tp, counter);
-    else if (twm == 2 && !TAPE) hipLaunchKernelGGL((trace_kernel<T, S, 2, UNI, false, SCH>), grid, blk, 0, s, jobs, tp, counter);
-    else hipLaunchKernelGGL((trace_kernel<T, S, 0, UNI, TAPE, SCH>), grid, blk, 0, s, jobs, tp, counter);
-}
-
-template <typename T, typename S, bool UNI>
-void launch_m2(int twm, dim3 grid, dim3 blk, hipStream_t s, const TraceJob *jobs,
-               const TraceParams &tp, unsigned long long *counter)
-{
-    if (twm == 1) hipLaunchKernelGGL((trace_kernel<T, S, 1, UNI, false, SCH_RKF45, true>), grid, blk, 0, s, jobs, tp, counter);
-    else hipLaunchKernelGGL((trace_kernel<T, S, 0, UNI, false, SCH_RKF45, true>), grid, blk, 0, s, jobs, tp, counter);
+        if (twm == 3) return (const void *)trace_kernel<T, S, 3, UNI, TAPE, SCH, false, CYL>;
+    if constexpr (!TAPE)
+        if (twm == 2) return (const void *)trace_kernel<T, S, 2, UNI, TAPE, SCH, false, CYL>;
+    return twm == 1 ? (const void *)trace_kernel<T, S, 1, UNI, TAPE, SCH, false, CYL>
+                    : (const void *)trace_kernel<T, S, 0, UNI, TAPE, SCH, false, CYL>;
 }
 
 template <typename T, typename S, bool UNI, bool TAPE>
-void launch_ts(int twm, dim3 grid, dim3 blk, hipStream_t s, const TraceJob *jobs,
-               const TraceParams &tp, unsigned long long *counter)
+const void *kernel_of(int twm, const TraceParams &tp)
 {
-    if (!TAPE && tp.method == FQ_METHOD_II) launch_m2<T, S, UNI>(twm, grid, blk, s, jobs, tp, counter);
-    else if (tp.scheme == SCH_RKF45) launch_tss<T, S, UNI, TAPE, SCH_RKF45>(twm, grid, blk, s, jobs, tp, counter);
-    else if (tp.scheme == SCH_RK4) launch_tss<T, S, UNI, TAPE, SCH_RK4>(twm, grid, blk, s, jobs, tp, counter);
-    else launch_tss<T, S, UNI, TAPE, SCH_RK4_38>(twm, grid, blk, s, jobs, tp, counter);
+    if constexpr (!TAPE)
+        if (tp.method == FQ_METHOD_II)
+            return twm == 1 ? (const void *)trace_kernel<T, S, 1, UNI, false, SCH_RKF45, true>
+                            : (const void *)trace_kernel<T, S, 0, UNI, false, SCH_RKF45, true>;
+    if constexpr (!TAPE && !UNI)
+        if (tp.cyl) return kernel_of_s<T, S, false, false, SCH_RKF45, true>(twm);
+    if constexpr (!TAPE || UNI) {
+        if (tp.scheme == SCH_RK4) return kernel_of_s<T, S, UNI, TAPE, SCH_RK4, false>(twm);
+        if (tp.scheme == SCH_RK4_38) return kernel_of_s<T, S, UNI, TAPE, SCH_RK4_38, false>(twm);
+    }
+    return kernel_of_s<T, S, UNI, TAPE, SCH_RKF45, false>(twm);
 }
 
 __global__ void fill_counts_kernel(uint32_t *counts)
@@ -1015,37 +1005,15 @@ hipError_t launch_bucket_order(int64_t n, int32_t *key, uint32_t *counts, int32_
 }
 
 namespace {
-// The kernel a launch_trace call picks (no tape) and the blocks per CU its grid has.
-const void *pick_kernel(int prec, int store, int twm, const TraceParams &tp)
+// FP32 arithmetic reads FP32 records, FP64 arithmetic either; the adjoint's forward pass
+// (tape) the records of its own type. Stretched grids take the multi-job kernels, which
+// carry their per-cell scales, except in the adjoint's single-job pass, which does too.
+template <bool TAPE> const void *kernel_for(bool f64, bool s64, bool uni, int twm, const TraceParams &tp)
 {
-    const bool f64 = prec == FQ_PREC_F64, s64 = store == FQ_DT_F64;
-    // stretched grids take the multi-job kernels, which carry their per-cell scales
-    const bool uni = tp.njobs == 1 && !tp.dynamic_last && !tp.stretched && !tp.cyl;
-    const int sch = tp.scheme, mt = tp.method;
-    if (!f64) return uni ? kernel_of<float, float, true>(twm, sch, mt) : kernel_of<float, float, false>(twm, sch, mt);
-    if (s64) return uni ? kernel_of<double, double, true>(twm, sch, mt) : kernel_of<double, double, false>(twm, sch, mt);
-    return uni ? kernel_of<double, float, true>(twm, sch, mt) : kernel_of<double, float, false>(twm, sch, mt);
-}
-
-int cu_count()
-{
-    int dev = 0, ncu = 0;
-    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) ncu = 0;
-    return ncu > 0 ? ncu : 256;
-}
-
-int blocks_per_cu(const void *fn, int block, int waves_per_cu)
-{
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, block, 0) != hipSuccess) per_cu = 0;
-    if (per_cu <= 0) per_cu = 1;
-    if (waves_per_cu > 0) {
-        const int want = (waves_per_cu * 64 + block - 1) / block;
-        if (want < per_cu) per_cu = want;
-        if (per_cu < 1) per_cu = 1;
-    }
-    return per_cu;
+    if (!f64) return uni ? kernel_of<float, float, true, TAPE>(twm, tp) : kernel_of<float, float, false, TAPE>(twm, tp);
+    if constexpr (!TAPE)
+        if (!s64) return uni ? kernel_of<double, float, true, TAPE>(twm, tp) : kernel_of<double, float, false, TAPE>(twm, tp);
+    return uni ? kernel_of<double, double, true, TAPE>(twm, tp) : kernel_of<double, double, false, TAPE>(twm, tp);
 }
 }  // namespace
 
@@ -1053,47 +1021,46 @@ hipError_t launch_trace(int prec, int store, int twm, const TraceJob *jobs_dev,
                         const TraceParams &tp, unsigned long long *counter, int block,
                         int waves_per_cu, hipStream_t s)
 {
-    const int ncu = cu_count();
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
+    int ncu = 0;
+    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) ncu = 0;
+    if (ncu <= 0) ncu = 256;
     if (block <= 0) block = 256;
     const bool f64 = prec == FQ_PREC_F64, s64 = store == FQ_DT_F64;
     if (!f64 && s64) return hipErrorInvalidValue;  // FP32 arithmetic reads FP32 records only
-    const bool uni = tp.njobs == 1 && !tp.dynamic_last && !tp.stretched && !tp.cyl;
     if (tp.scheme < SCH_RKF45 || tp.scheme > SCH_RK4_38) return hipErrorInvalidValue;
+    if (tp.cyl && tp.scheme != SCH_RKF45) return hipErrorInvalidValue;
+    const bool one = tp.njobs == 1 && !tp.dynamic_last;
+    const void *fn;
     if (tp.tape) {
         // the adjoint's forward pass, Method I, no FP64 re-trace list; FP64 on FP64
         // records, or the FP32 pass of the F32X form. One job (the single-job kernels,
         // which carry the stretched-grid lane state for it), or a seed plane and its
         // rotated-S0 job (the multi-job kernels, RKF45).
-        const bool one = tp.njobs == 1 && !tp.dynamic_last;
         const bool two = tp.njobs == 2 && tp.dynamic_last && tp.scheme == SCH_RKF45;
-        if (!(one || two) || tp.cyl || tp.list || tp.seg < 1 || tp.method != FQ_METHOD_I || f64 != s64)
+        if (!(one || two) || tp.cyl || tp.list || tp.seg < 1 || tp.method != FQ_METHOD_I || f64 != s64 || twm > 1)
             return hipErrorInvalidValue;
-        const dim3 grid((unsigned)(2 * ncu)), blk(256);
-        if (one) {
-            if (s64) launch_ts<double, double, true, true>(twm, grid, blk, s, jobs_dev, tp, counter);
-            else launch_ts<float, float, true, true>(twm, grid, blk, s, jobs_dev, tp, counter);
-        } else if (s64) {
-            launch_tss<double, double, false, true, SCH_RKF45>(twm, grid, blk, s, jobs_dev, tp, counter);
-        } else {
-            launch_tss<float, float, false, true, SCH_RKF45>(twm, grid, blk, s, jobs_dev, tp, counter);
-        }
-        return hipGetLastError();
-    }
-    if (tp.method == FQ_METHOD_II && (tp.scheme != SCH_RKF45 || twm == 2 || twm == 3)) return hipErrorInvalidValue;
-    if (twm == 3 && !f64) return hipErrorInvalidValue;
-    const int per_cu = blocks_per_cu(pick_kernel(prec, store, twm, tp), block, waves_per_cu);
-    dim3 grid((unsigned)(per_cu * ncu)), blk((unsigned)block);
-    if (!f64) {
-        if (uni) launch_ts<float, float, true, false>(twm, grid, blk, s, jobs_dev, tp, counter);
-        else launch_ts<float, float, false, false>(twm, grid, blk, s, jobs_dev, tp, counter);
-    } else if (s64) {
-        if (uni) launch_ts<double, double, true, false>(twm, grid, blk, s, jobs_dev, tp, counter);
-        else launch_ts<double, double, false, false>(twm, grid, blk, s, jobs_dev, tp, counter);
+        fn = kernel_for<true>(f64, s64, one, twm, tp);
+        block = 256;
+        waves_per_cu = 0;
     } else {
-        if (uni) launch_ts<double, float, true, false>(twm, grid, blk, s, jobs_dev, tp, counter);
-        else launch_ts<double, float, false, false>(twm, grid, blk, s, jobs_dev, tp, counter);
+        if (tp.method == FQ_METHOD_II && (tp.scheme != SCH_RKF45 || tp.cyl || twm == 2 || twm == 3))
+            return hipErrorInvalidValue;
+        if (twm == 3 && !f64) return hipErrorInvalidValue;
+        fn = kernel_for<false>(f64, s64, one && !tp.stretched && !tp.cyl, twm, tp);
     }
-    return hipGetLastError();
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, block, 0) != hipSuccess) per_cu = 0;
+    if (per_cu <= 0) per_cu = 1;
+    if (waves_per_cu > 0) {
+        int want = (waves_per_cu * 64 + block - 1) / block;
+        if (want < per_cu) per_cu = want;
+        if (per_cu < 1) per_cu = 1;
+    }
+    TraceParams p = tp;
+    void *args[3] = {&jobs_dev, &p, &counter};
+    return hipLaunchKernel(fn, dim3((unsigned)(per_cu * ncu)), dim3((unsigned)block), args, 0, s);
 }
 
 namespace {

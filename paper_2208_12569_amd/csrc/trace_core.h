@@ -103,6 +103,16 @@ __host__ __device__ __forceinline__ float pow01(float x)
 #endif
 }
 
+// x is computed where this stands. (The twist sum is used only where a step is accepted;
+// left to itself the compiler moves the whole twist integrand there and holds every
+// stage's position and field in registers until then.)
+template <typename T> __host__ __device__ __forceinline__ void here_and_now(T &x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(x));
+#endif
+}
+
 template <typename T> __host__ __device__ __forceinline__ T mn(T a, T b) { return a < b ? a : b; }
 template <typename T> __host__ __device__ __forceinline__ T mx(T a, T b) { return a > b ? a : b; }
 template <typename T> __host__ __device__ __forceinline__ bool finite_(T x)
@@ -494,6 +504,7 @@ __host__ __device__ __forceinline__ void lane_iterate(Lane<T> &L, const T cb[3][
         else bs = st == 2 ? B2 : st == 3 ? B3 : st == 4 ? B4 : st == 5 ? B5 : T(0);
         if (FIXED || st != 1) stw = N::fma_(bs, gts * ig, stw);
         if (FIXED || st != 1) slen = N::fma_(bs, ig, slen);
+        if (TW) here_and_now(stw);
     }
     // displacement and new position (the sum of the two rounded once), error
     T dy[3], e[3], nw[3];
