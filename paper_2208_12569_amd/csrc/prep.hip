@@ -65,58 +65,136 @@ template <typename T> struct V4;
 template <> struct V4<float> { using t = float4; };
 template <> struct V4<double> { using t = double4; };
 
-template <typename S, typename T>
+// A block takes a 64 x 4 patch of x and z and marches along y through `depth` rows, kRows
+// at a time: it asks for all of their values before it computes the first, since the pass
+// waits on memory and what counts is how much a wave has on its way (with one row at a
+// time it waited 90% of its time at 1.8 TB/s). A thread keeps its column's Bx and Bz of
+// the rows below and at its node; the x and z neighbours are mostly other lanes' own
+// values, in the caches: consecutive patches go to one XCD (blocks are dealt to the 8 XCDs
+// in turn), x fastest, then z. A wave's records leave through LDS in the order they have
+// in memory, 16 bytes a lane, so that every store fills whole lines.
+// The bound is memory, 12 bytes read and 32 written per FP32 node. Against one row piece
+// of 256 nodes per block iteration: 512x512x256 1.57 -> 0.70 ms (4.2 TB/s; a device copy
+// reaches 5.1), 384^3 1.70 -> 0.60 ms, 256x256x128 0.19 -> 0.10 ms, 64^3 (where most lanes
+// were past the row's end) 35 -> 19 us; FP32 planes to FP64 records of 384^3 2.39 -> 1.01 ms.
+constexpr int kRows = 4;
+
+template <typename S, typename T, bool TW>
 __global__ __launch_bounds__(256) void prep_kernel(const S *__restrict__ bx,
                                                    const S *__restrict__ by,
                                                    const S *__restrict__ bz, int nx, int ny,
                                                    int nz, double ihx, double ihy, double ihz,
                                                    const double *__restrict__ cx,
                                                    const double *__restrict__ cy,
-                                                   const double *__restrict__ cz, int want_tw,
-                                                   typename V4<T>::t *__restrict__ A,
+                                                   const double *__restrict__ cz, int tx, int tz,
+                                                   int depth, typename V4<T>::t *__restrict__ A,
                                                    float *__restrict__ bmax2)
 {
-    // a block takes a contiguous range of 256-node pieces of x rows (few blocks, so
-    // the maximum of |B|^2 costs one atomic per block): the rows next to a row in y
-    // are its own block's, and those next to it in z belong to blocks a fixed
-    // distance away in the grid, which run at the same time on the same XCD, so the
-    // neighbour reads of the curl differences mostly hit L2
-    const int bxs = (nx + 255) / 256;
-    const int64_t pieces = (int64_t)bxs * ny * nz;
+// sums and differences round as written
+#pragma clang fp contract(off)
+    using V = typename V4<T>::t;
+    // 16-byte pieces of the four waves' 64 records
+    typedef float Piece __attribute__((ext_vector_type(4)));
+    constexpr int kPieces = 2 * sizeof(V) / sizeof(Piece);
+    __shared__ Piece out[TW ? 4 : 1][TW ? 64 * kPieces : 1];
+    const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
     const int64_t nxy = (int64_t)nx * ny;
-    const int64_t per = (pieces + gridDim.x - 1) / gridDim.x;
-    const int64_t p_end = min(pieces, ((int64_t)blockIdx.x + 1) * per);
+    // patch of this block: gridDim.x / 8 consecutive ones per XCD (the grid is rounded up)
+    const int64_t pt = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    const int64_t pxz = (int64_t)tx * tz;
+    const int yc = (int)(pt / pxz);
+    const int r = (int)(pt - yc * pxz);
+    const int kb = r / tx, ib = r - kb * tx;
+    const int i = ib * 64 + lane, k = kb * 4 + w;
+    const int64_t j0 = (int64_t)yc * depth;
+    const int j1 = (int)min((int64_t)ny, j0 + depth);
+    const bool in = i < nx;
     float local = 0.0f;
-    for (int64_t piece = (int64_t)blockIdx.x * per; piece < p_end; piece++) {
-        const int64_t row = piece / bxs;
-        const int i = (int)(piece - row * bxs) * 256 + (int)threadIdx.x;
-        const int k = (int)(row / ny);
-        const int j = (int)(row - (int64_t)k * ny);
-        if (i >= nx) continue;
-        const int64_t q = (int64_t)k * nxy + (int64_t)j * nx + i;
-        const double Bx = ld(bx, q), By = ld(by, q), Bz = ld(bz, q);
-        typename V4<T>::t a;
-        a.x = (T)Bx;
-        a.y = (T)By;
-        a.z = (T)Bz;
-        if (want_tw) {
-            const double Jx = dax(bz, q, j, ny, nx, ihy, cy) - dax(by, q, k, nz, nxy, ihz, cz);
-            const double Jy = dax(bx, q, k, nz, nxy, ihz, cz) - dax(bz, q, i, nx, 1, ihx, cx);
-            const double Jz = dax(by, q, i, nx, 1, ihx, cx) - dax(bx, q, j, ny, nx, ihy, cy);
-            a.w = (T)Jx;
-            typename V4<T>::t c;
-            c.x = (T)Jy;
-            c.y = (T)Jz;
-            c.z = (T)0;
-            c.w = (T)0;
-            A[2 * q] = a;
-            A[2 * q + 1] = c;
-        } else {
-            a.w = (T)0;
-            A[q] = a;
+    if (k < nz && j0 < ny) {  // uniform in a wave
+        const int iq = in ? i : nx - 1;
+        int64_t q = (int64_t)k * nxy + j0 * nx + iq;
+        // interior nodes of uniform axes take the central differences from values loaded
+        // here; the others go through dax (one-sided or unequal spacings)
+        const bool zin = !cz && k > 0 && k < nz - 1, xin = !cx && iq > 0 && iq < nx - 1;
+        const int64_t zs = zin ? nxy : 0, xs = xin ? 1 : 0;
+        // Bx and Bz one row below and at the node
+        S xm = S(0), zm = S(0), x0 = bx[q], z0 = bz[q];
+        if (TW && j0 > 0) xm = bx[q - nx], zm = bz[q - nx];
+        for (int jr = (int)j0; jr < j1; jr += kRows) {
+            // all of these rows' values first: the pass waits on memory, so what counts is
+            // how much a wave has on its way at once
+            S X[kRows + 2], Z[kRows + 2], Y[kRows], Xl[kRows], Xh[kRows], Yl[kRows], Yh[kRows], Zw[kRows], Ze[kRows],
+                Yw[kRows], Ye[kRows];
+            X[0] = xm, X[1] = x0, Z[0] = zm, Z[1] = z0;
+#pragma unroll
+            for (int v = 0; v < kRows; v++) {
+                const int64_t p = q + (int64_t)min(v, ny - 1 - jr) * nx;
+                const int64_t pn = q + (int64_t)min(v + 1, ny - 1 - jr) * nx;
+                X[v + 2] = bx[pn];
+                Z[v + 2] = bz[pn];
+                Y[v] = by[p];
+                if (TW) {
+                    Xl[v] = bx[p - zs], Xh[v] = bx[p + zs];
+                    Yl[v] = by[p - zs], Yh[v] = by[p + zs];
+                    Zw[v] = bz[p - xs], Ze[v] = bz[p + xs];
+                    Yw[v] = by[p - xs], Ye[v] = by[p + xs];
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < kRows; v++) {
+                const int j = jr + v;
+                if (j >= j1) break;
+                const int64_t p = q + (int64_t)v * nx;
+                const double dx0 = (double)X[v + 1], dy0 = (double)Y[v], dz0 = (double)Z[v + 1];
+                V a, c;
+                a.x = (T)dx0;
+                a.y = (T)dy0;
+                a.z = (T)dz0;
+                a.w = (T)0;
+                if (TW) {
+                    double dyx = ((double)X[v + 2] - (double)X[v]) * (0.5 * ihy);
+                    double dyz = ((double)Z[v + 2] - (double)Z[v]) * (0.5 * ihy);
+                    double dzx = ((double)Xh[v] - (double)Xl[v]) * (0.5 * ihz);
+                    double dzy = ((double)Yh[v] - (double)Yl[v]) * (0.5 * ihz);
+                    double dxz = ((double)Ze[v] - (double)Zw[v]) * (0.5 * ihx);
+                    double dxy = ((double)Ye[v] - (double)Yw[v]) * (0.5 * ihx);
+                    if (cy || j == 0 || j == ny - 1) {
+                        dyx = dax(bx, p, j, ny, nx, ihy, cy);
+                        dyz = dax(bz, p, j, ny, nx, ihy, cy);
+                    }
+                    if (!zin) {
+                        dzx = dax(bx, p, k, nz, nxy, ihz, cz);
+                        dzy = dax(by, p, k, nz, nxy, ihz, cz);
+                    }
+                    if (!xin) {
+                        dxz = dax(bz, p, iq, nx, 1, ihx, cx);
+                        dxy = dax(by, p, iq, nx, 1, ihx, cx);
+                    }
+                    a.w = (T)(dyz - dzy);
+                    c.x = (T)(dzx - dxz);
+                    c.y = (T)(dxy - dyx);
+                    c.z = (T)0;
+                    c.w = (T)0;
+                    // the wave's 64 records in memory order (a wave's own rows: no barrier)
+                    V *own = (V *)&out[w][kPieces * lane];
+                    own[0] = a;
+                    own[1] = c;
+                    __builtin_amdgcn_wave_barrier();
+                    Piece *row = (Piece *)(A + 2 * ((int64_t)k * nxy + (int64_t)j * nx + ib * 64));
+                    const int live = kPieces * min(64, nx - ib * 64);
+#pragma unroll
+                    for (int u = 0; u < kPieces; u++)
+                        if (lane + 64 * u < live) row[lane + 64 * u] = out[w][lane + 64 * u];
+                    __builtin_amdgcn_wave_barrier();
+                } else if (in) {
+                    A[p] = a;
+                }
+                const float fb2 = (float)(dx0 * dx0 + dy0 * dy0 + dz0 * dz0);
+                if (in && fb2 > local) local = fb2;  // NaN compares false and is skipped
+            }
+            xm = X[kRows], zm = Z[kRows], x0 = X[kRows + 1], z0 = Z[kRows + 1];
+            q += (int64_t)kRows * nx;
         }
-        const float fb2 = (float)(Bx * Bx + By * By + Bz * Bz);
-        if (fb2 > local) local = fb2;  // NaN compares false and is skipped
     }
     // block maximum, then one atomic per block (non-negative floats order like ints)
     for (int off = 32; off > 0; off >>= 1) {
@@ -124,14 +202,16 @@ __global__ __launch_bounds__(256) void prep_kernel(const S *__restrict__ bx,
         local = o > local ? o : local;
     }
     __shared__ float wmax[4];
-    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = local;
+    if (lane == 0) wmax[w] = local;
     __syncthreads();
     if (threadIdx.x == 0) {
         float m = 0.0f;
-        for (int w = 0; w < (int)(blockDim.x + 63) / 64; w++) m = wmax[w] > m ? wmax[w] : m;
+        for (int v = 0; v < 4; v++) m = wmax[v] > m ? wmax[v] : m;
         if (m > 0.0f) {
             if (m > FLT_MAX) m = FLT_MAX;
-            atomicMax((int *)bmax2, __float_as_int(m));
+            // (most blocks see a larger maximum there already: thousands of atomics on one
+            // word take longer than the pass)
+            if (m > *(volatile float *)bmax2) atomicMax((int *)bmax2, __float_as_int(m));
         }
     }
 }
@@ -195,13 +275,19 @@ __global__ void fill_u32_kernel(uint32_t *p, int64_t n, uint32_t v)
 template <typename S, typename T>
 hipError_t run_prep(const fq_field &f, int want_tw, void *A, float *bmax2, hipStream_t s)
 {
-    const int64_t pieces = ((f.n[0] + 255) / 256) * f.n[1] * f.n[2];
-    const unsigned blocks = (unsigned)(pieces < 4096 ? pieces : 4096);
-    hipLaunchKernelGGL((prep_kernel<S, T>), dim3(blocks), dim3(256), 0, s,
+    const int64_t tx = (f.n[0] + 63) / 64, tz = (f.n[2] + 3) / 4;
+    // rows per block: about 4096 blocks where the grid has them (16 per CU), and no more
+    // than 32 rows (the row before the first is read twice)
+    int64_t depth = tx * tz * f.n[1] / 4096;
+    depth = depth < 1 ? 1 : (depth > 32 ? 32 : depth);
+    int64_t blocks = tx * tz * ((f.n[1] + depth - 1) / depth);
+    blocks = (blocks + 7) / 8 * 8;
+    const auto fn = want_tw ? prep_kernel<S, T, true> : prep_kernel<S, T, false>;
+    hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(256), 0, s,
                        (const S *)f.b[0], (const S *)f.b[1], (const S *)f.b[2], (int)f.n[0],
                        (int)f.n[1], (int)f.n[2], 1.0 / f.spacing[0], 1.0 / f.spacing[1],
-                       1.0 / f.spacing[2], f.coord[0], f.coord[1], f.coord[2], want_tw,
-                       (typename V4<T>::t *)A, bmax2);
+                       1.0 / f.spacing[2], f.coord[0], f.coord[1], f.coord[2], (int)tx, (int)tz,
+                       (int)depth, (typename V4<T>::t *)A, bmax2);
     return hipGetLastError();
 }
 
