@@ -298,12 +298,18 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
     for (int i = 0; i < ns; i++)
         if (stretched(specs[i].f) && m2) return FQ_EUNSUPPORTED;
     Carve cv;
-    // queue counters: +0 the tracer (u64, u32 spare), +64 the reverse pass, +128 the
-    // checkpoint pool, +192 the FP64 pass over half lines that need their twist
+    // Everything that starts from zero comes first, so that one launch clears it. Queue
+    // counters: +0 the tracer, +64 the FP64 pass and later the reverse pass (which clears
+    // it itself), +128 the checkpoint pool, +192 the FP64 pass over half lines that need
+    // their twist
     const size_t off_ctr = cv.take(256);
     // per-XCD queue counters of a 3-D map (8, 64 bytes apart)
     const bool xcd = ns == 1 && specs[0].kind == SPEC_VOXELS;
     const size_t off_xctr = xcd ? cv.take(512) : 0;
+    // the FP64 pass's list counts (positions only, twist), then per field max |B|^2 and
+    // the rotated-S0 entries
+    const size_t off_lcount = cv.take((2 + 2 * (size_t)ns) * sizeof(uint32_t));
+    const size_t zeroed = cv.off;
     std::vector<SpecWs> W(ns);
     int nrot = 0;
     for (int i = 0; i < ns; i++) {
@@ -313,7 +319,8 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
         const int64_t nn = nodes_of(s.f);
         w.nlines = lines_of(s);
         w.nodes = cv.take((size_t)nn * (P.want_tw ? 8 : 4) * tsz);
-        w.bmax = cv.take(sizeof(float));
+        w.bmax = off_lcount + (2 + 2 * (size_t)i) * sizeof(uint32_t);
+        w.rot_count = w.bmax + sizeof(uint32_t);
         take_recs(cv, w.nlines, w.end, w.tw, w.len, w.face, w.st);
         if (s.kind == SPEC_PLANE || s.kind == SPEC_VOXELS) {
             const int64_t ntiles = s.kind == SPEC_PLANE
@@ -334,7 +341,6 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
             nrot++;
             w.rot_index = cv.take((size_t)w.nlines * sizeof(int32_t));
             w.rot = cv.take((size_t)w.nlines * sizeof(RotEntry));
-            w.rot_count = cv.take(sizeof(uint32_t));
             take_recs(cv, 4 * w.nlines, w.r_end, w.r_tw, w.r_len, w.r_face, w.r_st);
         }
     }
@@ -350,10 +356,9 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
         if (specs[i].f->dtype == FQ_DT_F64) fix_store = FQ_DT_F64;
     int64_t all_lines = 0;
     for (int i = 0; i < ns; i++) all_lines += W[i].nlines * (W[i].rotate ? 5 : 1);
-    size_t off_list = 0, off_lcount = 0, off_jobs64 = 0, off_fkey = 0, off_fcnt = 0, off_flist = 0;
+    size_t off_list = 0, off_jobs64 = 0, off_fkey = 0, off_fcnt = 0, off_flist = 0;
     if (fixup) {
         off_list = cv.take((size_t)(2 * all_lines) * sizeof(FixEntry));
-        off_lcount = cv.take(2 * sizeof(uint32_t));  // positions-only and twist lists
         if (P.in_flight) {
             // the positions-only list ordered longest first (keys, counts, the list)
             off_fkey = cv.take((size_t)(2 * all_lines) * sizeof(int32_t));
@@ -411,12 +416,10 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
     const bool fwd = !bwd || bwd->phase != 2;
     const bool rev = bwd && bwd->phase != 1;
     unsigned long long *counter = (unsigned long long *)(ws + off_ctr);
-    if (fwd) FQ_TRY(launch_fill_u32((uint32_t *)(ws + off_ctr), 4, 0u, stream));
+    if (fwd) FQ_TRY(launch_fill_u32((uint32_t *)ws, (int64_t)(zeroed / sizeof(uint32_t)), 0u, stream));
     for (int i = 0; i < ns && fwd; i++) {
         const Spec &s = specs[i];
         SpecWs &w = W[i];
-        FQ_TRY(launch_fill_u32((uint32_t *)(ws + w.bmax), 1, 0u, stream));
-        if (w.rotate) FQ_TRY(launch_fill_u32((uint32_t *)(ws + w.rot_count), 1, 0u, stream));
         if (stretched(s.f)) {
             double *const iw[3] = {(double *)(ws + w.iw[0]), (double *)(ws + w.iw[1]),
                                    (double *)(ws + w.iw[2])};
@@ -607,10 +610,7 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
     tp.max_steps = P.max_steps;
     tp.want_tw = P.want_tw;
     tp.njobs = njobs;
-    if (xcd) {
-        tp.xcd_ctr = (unsigned long long *)(ws + off_xctr);
-        if (fwd) FQ_TRY(launch_fill_u32((uint32_t *)(ws + off_xctr), 128, 0u, stream));
-    }
+    if (xcd) tp.xcd_ctr = (unsigned long long *)(ws + off_xctr);
     tp.stats = bwd ? nullptr : (unsigned long long *)P.stats;
     tp.static_items = items;
     if (bwd) {
@@ -622,7 +622,6 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
         tp.seg = bwd->seg;
         tp.pool_cap = bwd->pool;
         tp.tape_base1 = 2 * W[0].nlines;
-        if (fwd) FQ_TRY(launch_fill_u32((uint32_t *)(ws + off_ctr + 128), 2, 0u, stream));
     }
     hipEvent_t *ev = fwd ? (hipEvent_t *)P.events : nullptr;
     if (ev && ev[0]) FQ_TRY(hipEventRecord(ev[0], stream));
@@ -650,8 +649,6 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
         const bool split = P.want_tw && !m2;
         FixEntry *list = (FixEntry *)(ws + off_list);
         uint32_t *lcount = (uint32_t *)(ws + off_lcount);
-        FQ_TRY(launch_fill_u32(lcount, 2, 0u, stream));
-        FQ_TRY(launch_fill_u32((uint32_t *)(ws + off_ctr), 2, 0u, stream));
         for (int j = 0; j < njobs; j++) {
             // the spec whose map decides the Q rule: a main job's own, or for the
             // rotated-S0 job the map of the spec it belongs to
@@ -698,8 +695,8 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
         // FP32 pass's Tw is kept and the latency-bound FP64 pass skips the curl
         // (with other maps in flight, the positions-only form at three waves per SIMD)
         const int fix_twm = !P.want_tw ? 0 : (split ? (P.in_flight ? 3 : 2) : 1);
-        FQ_TRY(launch_trace(FQ_PREC_F64, fix_store, fix_twm, fix_jobs, fp, counter, P.block,
-                            P.waves_per_cu, stream));
+        FQ_TRY(launch_trace(FQ_PREC_F64, fix_store, fix_twm, fix_jobs, fp,
+                            (unsigned long long *)(ws + off_ctr + 64), P.block, P.waves_per_cu, stream));
         if (split) {
             // half lines the FP32 pass could not finish have no twist yet: trace those
             // (usually none) with the twist integrand, on a queue counter of their own
@@ -707,10 +704,8 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
             ft.list = list;  // the twist list sits at the top of the unordered array
             ft.list_count = lcount + 1;
             ft.list_rev = 1;
-            unsigned long long *c2 = (unsigned long long *)(ws + off_ctr + 192);
-            FQ_TRY(launch_fill_u32((uint32_t *)c2, 2, 0u, stream));
-            FQ_TRY(launch_trace(FQ_PREC_F64, fix_store, 1, fix_jobs, ft, c2, P.block, P.waves_per_cu,
-                                stream));
+            FQ_TRY(launch_trace(FQ_PREC_F64, fix_store, 1, fix_jobs, ft,
+                                (unsigned long long *)(ws + off_ctr + 192), P.block, P.waves_per_cu, stream));
         }
         if (ev && ev[3]) FQ_TRY(hipEventRecord(ev[3], stream));
     }

@@ -211,7 +211,7 @@ hipError_t launch_bucket_order(int64_t n, int32_t *key, uint32_t *counts, int32_
                                hipStream_t s);
 // Order the tiles of a plane job (J: its host copy; its node records, written by
 // the prep pass for precision prec and want_tw, valid on the device): bucket (tiles),
-// counts (256), order (tiles) are workspace arrays.
+// counts (256; 65536 for voxels), order (tiles) are workspace arrays.
 hipError_t launch_tile_order(const TraceJob &J, int prec, int want_tw, int32_t *bucket, uint32_t *counts,
                              int32_t *order, hipStream_t s);
 hipError_t launch_voxel_order(const TraceJob &J, int prec, int want_tw, int32_t *key,

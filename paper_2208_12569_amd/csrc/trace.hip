@@ -71,7 +71,11 @@ template <typename T> constexpr double kCylEnd() { return sizeof(T) == 4 ? 1e-5 
 // A wave refills its idle lanes only once at least this many are idle (or none is
 // busy): the refill code runs for the whole wave, so refilling one lane at a time
 // would run it on almost every iteration. FP64 steps cost more, so idle lanes cost more
-// there and the threshold is lower.
+// there and the threshold is lower. The waves of a 3-D map refill only when all their
+// lanes are idle: the 64 lines of a voxel tile then stay alone in their wave and gather
+// one neighbourhood, which is worth more there than the idle lanes (a 256x256x128 map of
+// a 512x512x256 cube 164 -> 153 ms, 128x128x64 of 256x256x128 13.8 -> 13.1 ms and 19.5 ->
+// 17.3 ms in FP64; at 40 lanes 160 ms, at 12 lanes 15% slower than at 24).
 template <typename T> constexpr int refill_min() { return sizeof(T) == 4 ? 24 : 8; }
 
 // TWM: 0 = no twist (narrow records), 1 = twist, 2 = positions only on wide records
@@ -186,7 +190,7 @@ __global__ __launch_bounds__(256, (waves_per_simd<T, TWM, M2, CYL>())) void trac
         // ---- refill idle lanes: one atomic per wave ------------------------------------
         const bool need = (jb < 0) && !exhausted;
         unsigned long long m = __ballot(need);
-        if (m && __popcll(m) < refill_min<T>() && __ballot(jb >= 0) != 0) m = 0;
+        if (m && __popcll(m) < (xsplit ? 64 : refill_min<T>()) && __ballot(jb >= 0) != 0) m = 0;
         if (m) {
             const int cnt = __popcll(m);
             const int leader = __ffsll((long long)m) - 1;
@@ -648,19 +652,40 @@ const void *kernel_of(int twm, const TraceParams &tp)
     return kernel_of_s<T, S, UNI, TAPE, SCH_RKF45, false>(twm);
 }
 
-__global__ void fill_counts_kernel(uint32_t *counts)
+// Bucket sorts (longest first) have 128 buckets of two key values each: they count into
+// counts[0..127] and place through the cursors counts[128..255].
+constexpr int kBuckets = 128;
+
+__device__ __forceinline__ int bucket_of(int key)
+{
+    return kBuckets - 1 - (key < 0 ? 0 : (key > 255 ? 255 : key)) / 2;
+}
+
+__device__ __forceinline__ void clear_counts(uint32_t *counts)
 {
     counts[threadIdx.x] = 0u;
 }
 
+__global__ void fill_counts_kernel(uint32_t *counts)
+{
+    clear_counts(counts);
+}
+
 // Tile order of a plane job: long lines start early, so the last ones to finish are
 // short. A tile's key is the length of the longest of ten coarse half lines: its four
-// corner seeds and a central one, traced both ways with Heun steps of four grid
+// corner seeds and a central one, traced both ways with steps of four grid
 // spacings (at most 256), in FP32 on the tracer's own node records (B in the first
 // four values of a record of type R; 8-wide records when WIDE). Half lines are the
 // queue's items, so the longest half decides when a tile's work ends; the key is the
 // step count, and tiles are placed longest first (the order inside a key does not
 // matter: every line's result is independent of when it is traced).
+// The longest coarse line's chain of field evaluations is what these kernels take, so a
+// coarse step is second-order Adams-Bashforth, with one evaluation (the first step takes
+// the midpoint rule's two; with an Euler step there the order is worse, 4.94 instead of
+// 4.81 ms for the 1024 x 1024 map of 256x256x128): the pre-pass of that map 228 -> 117 us,
+// of 512 x 512 seeds on the stretched grid 450 -> 250 us, of 4x4x4 voxel tiles of a
+// 512x512x256 cube 1.1 -> 0.6 ms. Against the midpoint rule throughout, the order costs
+// that map 1% and gains a batch of 8 cubes 4.6% and the stretched map 3.4%.
 constexpr int kCoarseCells = 4, kCoarseSteps = 256;
 
 // B at grid coordinates g (clamped into the grid) from the node records.
@@ -692,76 +717,109 @@ __device__ __forceinline__ void coarse_field(const typename V4<R>::t *__restrict
     }
 }
 
+// One coarse line through a job's records, from grid coordinates g along sgn B, at most
+// `most` steps; returns the steps taken inside the box, `left` set if it left (g is then
+// past the face it left by).
 template <typename R, bool WIDE>
-__global__ void tile_len_kernel(TraceJob J, int32_t *__restrict__ len)
+__device__ __forceinline__ int coarse_line(const TraceJob &J, float g[3], float sgn, int most, bool &left)
 {
     const typename V4<R>::t *A = gptr((const typename V4<R>::t *)J.nodes);
-    const int64_t ntiles = J.tiles[0] * J.tiles[1];
     // stretched grids: grid coordinates run through the cells at their own widths,
     // so a coarse step's size in grid units follows the cell it starts in
     const bool str = J.geo != nullptr;
     const double dmin = str ? J.geo->dref : fmin(J.spacing[0], fmin(J.spacing[1], J.spacing[2]));
     const int n[3] = {J.n[0], J.n[1], J.n[2]};
     float hs[3];  // a coarse step along a unit direction, in grid units per axis
-    for (int a = 0; a < 3; a++) hs[a] = (float)(kCoarseCells * dmin / J.spacing[a]);
-    auto step_of = [&](int a, float ga) -> float {
-        if (!str) return hs[a];
-        const int c = min(max((int)floorf(ga), 0), n[a] - 2);
-        return (float)(kCoarseCells * dmin * J.iw[a][c]);
-    };
-    const int sw[5] = {0, 7, 56, 63, 36};
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < 10 * ntiles;
-         k += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t t = k / 10;
-        const int q = (int)(k - 10 * t);
-        const float sgn = (q & 1) ? -1.0f : 1.0f;
+    for (int a = 0; a < 3; a++) hs[a] = sgn * (float)(kCoarseCells * dmin / J.spacing[a]);
+    float d0[3] = {0.0f, 0.0f, 0.0f};
+    left = false;
+    int m = 0;
+    for (; m < most; m++) {
+        float B[3], st[3], d2[3] = {0.0f, 0.0f, 0.0f};
+        for (int a = 0; a < 3; a++) {
+            st[a] = hs[a];
+            if (str) {
+                const int c = min(max((int)floorf(g[a]), 0), n[a] - 2);
+                st[a] = sgn * (float)(kCoarseCells * dmin * J.iw[a][c]);
+            }
+        }
+        coarse_field<R, WIDE>(A, n, g, B);
+        const float bm = sqrtf(B[0] * B[0] + B[1] * B[1] + B[2] * B[2]);
+        if (!(bm > 0.0f) || !isfinite(bm)) break;
+        if (m == 0) {
+            float gm[3], B2[3];
+            for (int a = 0; a < 3; a++) gm[a] = g[a] + 0.5f * st[a] * B[a] / bm;
+            coarse_field<R, WIDE>(A, n, gm, B2);
+            const float bm2 = sqrtf(B2[0] * B2[0] + B2[1] * B2[1] + B2[2] * B2[2]);
+            if (!(bm2 > 0.0f) || !isfinite(bm2)) break;
+            for (int a = 0; a < 3; a++) d2[a] = st[a] * B2[a] / bm2;
+        }
+        for (int a = 0; a < 3; a++) {
+            const float d = st[a] * B[a] / bm;
+            g[a] += m == 0 ? d2[a] : 1.5f * d - 0.5f * d0[a];
+            d0[a] = d;
+            left = left || g[a] < 0.0f || g[a] > (float)(n[a] - 1);
+        }
+        if (left) break;
+    }
+    return m;
+}
+
+// Grid coordinates of seed (i, j, k); false outside the box.
+__device__ __forceinline__ bool seed_grid(const TraceJob &J, int64_t i, int64_t j, int64_t k, float g[3])
+{
+    bool inside = true;
+    for (int a = 0; a < 3; a++) {
+        const double r = J.s_origin[a] + (double)i * J.s_a[a] + (double)j * J.s_b[a] + (double)k * J.s_c[a];
+        if (J.geo != nullptr && J.planes.coord[a]) {
+            const double *x = J.planes.coord[a];
+            inside = inside && r >= x[0] && r <= x[J.n[a] - 1];
+            double p;
+            const int c = str_cell(J, a, r, p);
+            g[a] = (float)((double)c + p);
+            continue;
+        }
+        g[a] = (float)((r - J.origin[a]) * J.inv_spacing[a]);
+        inside = inside && g[a] >= 0.0f && g[a] <= (float)(J.n[a] - 1);
+    }
+    return inside;
+}
+
+// Ten lanes a tile, six tiles a wave. The first block also clears the bucket counts of
+// the sort that follows.
+template <typename R, bool WIDE>
+__global__ __launch_bounds__(256) void tile_len_kernel(TraceJob J, int32_t *__restrict__ len,
+                                                       uint32_t *__restrict__ counts)
+{
+    __shared__ int longest[4][6];
+    const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
+    if (blockIdx.x == 0) clear_counts(counts);
+    if (lane < 6) longest[w][lane] = 0;
+    __syncthreads();
+    const int64_t ntiles = J.tiles[0] * J.tiles[1];
+    const int64_t t0 = ((int64_t)blockIdx.x * 4 + w) * 6;
+    const int sub = lane / 10, q = lane - 10 * sub;
+    const int64_t t = t0 + sub;
+    if (lane < 60 && t < ntiles) {
+        const int sw[5] = {0, 7, 56, 63, 36};
         const int64_t ty = t / J.tiles[0], tx = t - ty * J.tiles[0];
-        const int w = sw[q >> 1];
-        int64_t i = tx * 8 + (w & 7), j = ty * 8 + (w >> 3);
+        const int v = sw[q >> 1];
+        int64_t i = tx * 8 + (v & 7), j = ty * 8 + (v >> 3);
         i = i < J.dims[0] ? i : J.dims[0] - 1;
         j = j < J.dims[1] ? j : J.dims[1] - 1;
         float g[3];
-        bool inside = true;
-        for (int a = 0; a < 3; a++) {
-            const double r = J.s_origin[a] + (double)i * J.s_a[a] + (double)j * J.s_b[a];
-            if (str && J.planes.coord[a]) {
-                const double *x = J.planes.coord[a];
-                inside = inside && r >= x[0] && r <= x[n[a] - 1];
-                double p;
-                const int c = str_cell(J, a, r, p);
-                g[a] = (float)((double)c + p);
-                continue;
-            }
-            g[a] = (float)((r - J.origin[a]) * J.inv_spacing[a]);
-            inside = inside && g[a] >= 0.0f && g[a] <= (float)(n[a] - 1);
-        }
-        int m = 0;
-        if (inside) {
-            for (; m < kCoarseSteps; m++) {
-                float B[3], gm[3], B2[3];
-                coarse_field<R, WIDE>(A, n, g, B);
-                const float bm = sqrtf(B[0] * B[0] + B[1] * B[1] + B[2] * B[2]);
-                if (!(bm > 0.0f) || !isfinite(bm)) break;
-                for (int a = 0; a < 3; a++) gm[a] = g[a] + 0.5f * sgn * step_of(a, g[a]) * B[a] / bm;
-                coarse_field<R, WIDE>(A, n, gm, B2);
-                const float bm2 = sqrtf(B2[0] * B2[0] + B2[1] * B2[1] + B2[2] * B2[2]);
-                if (!(bm2 > 0.0f) || !isfinite(bm2)) break;
-                bool in = true;
-                for (int a = 0; a < 3; a++) {
-                    g[a] += sgn * step_of(a, gm[a]) * B2[a] / bm2;
-                    in = in && g[a] >= 0.0f && g[a] <= (float)(n[a] - 1);
-                }
-                if (!in) break;
-            }
-        }
-        atomicMax(len + t, m);
+        bool left;
+        if (seed_grid(J, i, j, 0, g))
+            atomicMax(&longest[w][sub], coarse_line<R, WIDE>(J, g, (q & 1) ? -1.0f : 1.0f, kCoarseSteps, left));
     }
+    __syncthreads();
+    if (lane < 6 && t0 + lane < ntiles) len[t0 + lane] = longest[w][lane];
 }
 
 // Tile order of a 3-D (voxel) job: a voxel map's lines sweep the whole cube, whose
 // node records do not fit the caches, so the tiles whose lines run together should be
 // traced together. Lines that share a footpoint are one flux tube: a tile's key is
-// where the coarse backward line from its central voxel leaves the box (Heun steps
+// where the coarse backward line from its central voxel leaves the box (steps
 // of four grid spacings, at most 1024), a bin of that face, the bins of each face in
 // a serpentine order so that neighbouring keys are neighbouring bins: 224 x 224 bins
 // on the bottom face (z low, where most lines of a solar cube end), 50 x 60 on each
@@ -778,74 +836,34 @@ __device__ __forceinline__ int serp(float u, float v, int nu, int nv)
 }
 
 template <typename R, bool WIDE>
-__global__ void tile_foot_kernel(TraceJob J, int32_t *__restrict__ key)
+__global__ __launch_bounds__(256) void tile_foot_kernel(TraceJob J, int32_t *__restrict__ key)
 {
-    const typename V4<R>::t *A = gptr((const typename V4<R>::t *)J.nodes);
     const int64_t ntiles = J.tiles[0] * J.tiles[1] * J.tiles[2];
-    const bool str = J.geo != nullptr;
-    const double dmin = str ? J.geo->dref : fmin(J.spacing[0], fmin(J.spacing[1], J.spacing[2]));
     const int n[3] = {J.n[0], J.n[1], J.n[2]};
-    float hs[3];
-    for (int a = 0; a < 3; a++) hs[a] = (float)(kCoarseCells * dmin / J.spacing[a]);
-    auto step_of = [&](int a, float ga) -> float {
-        if (!str) return hs[a];
-        const int c = min(max((int)floorf(ga), 0), n[a] - 2);
-        return (float)(kCoarseCells * dmin * J.iw[a][c]);
-    };
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < ntiles;
          t += (int64_t)gridDim.x * blockDim.x) {
         const int64_t tz = t / (J.tiles[0] * J.tiles[1]);
         const int64_t rem = t - tz * J.tiles[0] * J.tiles[1];
         const int64_t ty = rem / J.tiles[0], tx = rem - ty * J.tiles[0];
-        const int64_t iv[3] = {min(tx * 4 + 2, J.dims[0] - 1), min(ty * 4 + 2, J.dims[1] - 1),
-                               min(tz * 4 + 2, J.dims[2] - 1)};
-        const double sp[3] = {J.s_a[0], J.s_b[1], J.s_c[2]};
         float g[3];
-        bool inside = true;
-        for (int a = 0; a < 3; a++) {
-            const double r = J.s_origin[a] + (double)iv[a] * sp[a];
-            if (str && J.planes.coord[a]) {
-                const double *x = J.planes.coord[a];
-                inside = inside && r >= x[0] && r <= x[n[a] - 1];
-                double p;
-                const int c = str_cell(J, a, r, p);
-                g[a] = (float)((double)c + p);
-                continue;
-            }
-            g[a] = (float)((r - J.origin[a]) * J.inv_spacing[a]);
-            inside = inside && g[a] >= 0.0f && g[a] <= (float)(n[a] - 1);
-        }
+        bool left = false;
+        if (seed_grid(J, min(tx * 4 + 2, J.dims[0] - 1), min(ty * 4 + 2, J.dims[1] - 1),
+                      min(tz * 4 + 2, J.dims[2] - 1), g))
+            coarse_line<R, WIDE>(J, g, -1.0f, kFootSteps, left);
         int k = kFootKeys - 1;
-        if (inside) {
-            bool left = false;
-            for (int m = 0; m < kFootSteps && !left; m++) {
-                float B[3], gm[3], B2[3];
-                coarse_field<R, WIDE>(A, n, g, B);
-                const float bm = sqrtf(B[0] * B[0] + B[1] * B[1] + B[2] * B[2]);
-                if (!(bm > 0.0f) || !isfinite(bm)) break;
-                for (int a = 0; a < 3; a++) gm[a] = g[a] - 0.5f * step_of(a, g[a]) * B[a] / bm;
-                coarse_field<R, WIDE>(A, n, gm, B2);
-                const float bm2 = sqrtf(B2[0] * B2[0] + B2[1] * B2[1] + B2[2] * B2[2]);
-                if (!(bm2 > 0.0f) || !isfinite(bm2)) break;
-                for (int a = 0; a < 3; a++) {
-                    g[a] -= step_of(a, gm[a]) * B2[a] / bm2;
-                    left = left || g[a] < 0.0f || g[a] > (float)(n[a] - 1);
-                }
+        if (left) {
+            // the face it left by: the farthest out (grid units)
+            int f = 0;
+            float out = -1.0f;
+            for (int a = 0; a < 3; a++) {
+                const float lo = -g[a], hi = g[a] - (float)(n[a] - 1);
+                if (lo > out) out = lo, f = 2 * a;
+                if (hi > out) out = hi, f = 2 * a + 1;
             }
-            if (left) {
-                // the face it left by: the farthest out (grid units)
-                int f = 0;
-                float out = -1.0f;
-                for (int a = 0; a < 3; a++) {
-                    const float lo = -g[a], hi = g[a] - (float)(n[a] - 1);
-                    if (lo > out) out = lo, f = 2 * a;
-                    if (hi > out) out = hi, f = 2 * a + 1;
-                }
-                const int a = f >> 1, b = a == 0 ? 1 : 0, c = a == 2 ? 1 : 2;
-                const float u = g[b] / (float)(n[b] - 1), v = g[c] / (float)(n[c] - 1);
-                if (f == 4) k = serp(u, v, 224, 224);
-                else k = 224 * 224 + 3000 * (f < 4 ? f : 4) + serp(u, v, 50, 60);
-            }
+            const int a = f >> 1, b = a == 0 ? 1 : 0, c = a == 2 ? 1 : 2;
+            const float u = g[b] / (float)(n[b] - 1), v = g[c] / (float)(n[c] - 1);
+            if (f == 4) k = serp(u, v, 224, 224);
+            else k = 224 * 224 + 3000 * (f < 4 ? f : 4) + serp(u, v, 50, 60);
         }
         key[t] = k;
     }
@@ -861,8 +879,7 @@ __global__ void tile_key_kernel(int64_t ntiles, int32_t *__restrict__ bucket,
     __syncthreads();
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < ntiles;
          t += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t n = bucket[t];
-        const int b = 255 - (n < 0 ? 0 : (n > 255 ? 255 : n));
+        const int b = bucket_of(bucket[t]);
         bucket[t] = b;
         atomicAdd(hist + b, 1u);
     }
@@ -870,25 +887,35 @@ __global__ void tile_key_kernel(int64_t ntiles, int32_t *__restrict__ bucket,
     if (hist[threadIdx.x]) atomicAdd(counts + threadIdx.x, hist[threadIdx.x]);
 }
 
-__global__ void tile_scan_kernel(uint32_t *counts)
+// Where each bucket starts: the exclusive scan of the counts, by a block of 256 (whose
+// upper half scans nothing).
+__device__ __forceinline__ void bucket_starts(const uint32_t *__restrict__ counts, uint32_t start[256])
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        uint32_t acc = 0;
-        for (int b = 0; b < 256; b++) {
-            const uint32_t c = counts[b];
-            counts[b] = acc;
-            acc += c;
-        }
+    const int t = (int)threadIdx.x;
+    const uint32_t c = t < kBuckets ? counts[t] : 0u;
+    start[t] = c;
+    __syncthreads();
+    for (int d = 1; d < kBuckets; d <<= 1) {
+        const uint32_t v = t >= d ? start[t - d] : 0u;
+        __syncthreads();
+        start[t] += v;
+        __syncthreads();
     }
+    const uint32_t e = start[t] - c;
+    __syncthreads();
+    start[t] = e;
+    __syncthreads();
 }
 
 // Each block ranks its tiles inside their buckets in LDS and takes one range per
 // bucket from the global offsets. Blocks of 256; every thread runs the same number
 // of iterations (the barriers are uniform).
 __global__ void tile_place_kernel(int64_t ntiles, const int32_t *__restrict__ bucket,
-                                  uint32_t *__restrict__ offsets, int32_t *__restrict__ order)
+                                  uint32_t *__restrict__ counts, int32_t *__restrict__ order)
 {
-    __shared__ uint32_t hist[256], base[256];
+    __shared__ uint32_t hist[256], base[256], start[256];
+    bucket_starts(counts, start);
+    uint32_t *cursor = counts + kBuckets;
     for (int64_t t0 = (int64_t)blockIdx.x * blockDim.x; t0 < ntiles;
          t0 += (int64_t)gridDim.x * blockDim.x) {
         const int64_t t = t0 + threadIdx.x;
@@ -897,11 +924,23 @@ __global__ void tile_place_kernel(int64_t ntiles, const int32_t *__restrict__ bu
         const int b = t < ntiles ? bucket[t] : -1;
         const uint32_t r = b >= 0 ? atomicAdd(hist + b, 1u) : 0u;
         __syncthreads();
-        if (hist[threadIdx.x]) base[threadIdx.x] = atomicAdd(offsets + threadIdx.x, hist[threadIdx.x]);
+        if (hist[threadIdx.x])
+            base[threadIdx.x] = start[threadIdx.x] + atomicAdd(cursor + threadIdx.x, hist[threadIdx.x]);
         __syncthreads();
         if (b >= 0) order[base[b] + r] = (int32_t)t;
         __syncthreads();
     }
+}
+
+// Sorts n items by key (cleared counts).
+hipError_t bucket_sort(int64_t n, int32_t *key, uint32_t *counts, int32_t *order, hipStream_t s)
+{
+    int64_t b = (n + 255) / 256;
+    if (b < 1) b = 1;
+    if (b > 4096) b = 4096;
+    hipLaunchKernelGGL(tile_key_kernel, dim3((unsigned)b), dim3(256), 0, s, n, key, counts);
+    hipLaunchKernelGGL(tile_place_kernel, dim3((unsigned)b), dim3(256), 0, s, n, key, counts, order);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -910,21 +949,18 @@ hipError_t launch_tile_order(const TraceJob &J, int prec, int want_tw, int32_t *
                              uint32_t *counts, int32_t *order, hipStream_t s)
 {
     const int64_t ntiles = J.tiles[0] * J.tiles[1];
-    hipError_t e = launch_fill_u32((uint32_t *)bucket, ntiles, 0u, s);
-    if (e != hipSuccess) return e;
-    int64_t bl = (10 * ntiles + 255) / 256;
-    if (bl > 65536) bl = 65536;
+    const unsigned bl = (unsigned)((ntiles + 23) / 24);
     // the node records the prep pass wrote: FP64 values for the all-FP64 form
     if (prec == FQ_PREC_F64) {
-        if (want_tw) hipLaunchKernelGGL((tile_len_kernel<double, true>), dim3((unsigned)bl), dim3(256), 0, s, J, bucket);
-        else hipLaunchKernelGGL((tile_len_kernel<double, false>), dim3((unsigned)bl), dim3(256), 0, s, J, bucket);
+        if (want_tw) hipLaunchKernelGGL((tile_len_kernel<double, true>), dim3(bl), dim3(256), 0, s, J, bucket, counts);
+        else hipLaunchKernelGGL((tile_len_kernel<double, false>), dim3(bl), dim3(256), 0, s, J, bucket, counts);
     } else {
-        if (want_tw) hipLaunchKernelGGL((tile_len_kernel<float, true>), dim3((unsigned)bl), dim3(256), 0, s, J, bucket);
-        else hipLaunchKernelGGL((tile_len_kernel<float, false>), dim3((unsigned)bl), dim3(256), 0, s, J, bucket);
+        if (want_tw) hipLaunchKernelGGL((tile_len_kernel<float, true>), dim3(bl), dim3(256), 0, s, J, bucket, counts);
+        else hipLaunchKernelGGL((tile_len_kernel<float, false>), dim3(bl), dim3(256), 0, s, J, bucket, counts);
     }
-    e = hipGetLastError();
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_bucket_order(ntiles, bucket, counts, order, s);
+    return bucket_sort(ntiles, bucket, counts, order, s);
 }
 
 namespace {
@@ -994,14 +1030,8 @@ hipError_t launch_voxel_order(const TraceJob &J, int prec, int want_tw, int32_t 
 hipError_t launch_bucket_order(int64_t n, int32_t *key, uint32_t *counts, int32_t *order,
                                hipStream_t s)
 {
-    int64_t b = (n + 255) / 256;
-    if (b < 1) b = 1;
-    if (b > 4096) b = 4096;
     hipLaunchKernelGGL(fill_counts_kernel, dim3(1), dim3(256), 0, s, counts);
-    hipLaunchKernelGGL(tile_key_kernel, dim3((unsigned)b), dim3(256), 0, s, n, key, counts);
-    hipLaunchKernelGGL(tile_scan_kernel, dim3(1), dim3(64), 0, s, counts);
-    hipLaunchKernelGGL(tile_place_kernel, dim3((unsigned)b), dim3(256), 0, s, n, key, counts, order);
-    return hipGetLastError();
+    return bucket_sort(n, key, counts, order, s);
 }
 
 namespace {
@@ -1108,8 +1138,7 @@ __global__ void fix_key_kernel(const TraceJob *__restrict__ jobs, const FixEntry
         if (J.spacing[1] < d) d = J.spacing[1];
         if (J.spacing[2] < d) d = J.spacing[2];
         const double c = len / (4.0 * d);
-        const int k = !(c > 0.0) ? 0 : (c >= 255.0 ? 255 : (int)c);
-        const int b = 255 - k;
+        const int b = bucket_of(!(c > 0.0) ? 0 : (c >= 255.0 ? 255 : (int)c));
         key[t] = b;
         atomicAdd(hist + b, 1u);
     }
@@ -1119,9 +1148,11 @@ __global__ void fix_key_kernel(const TraceJob *__restrict__ jobs, const FixEntry
 
 __global__ void fix_place_kernel(const FixEntry *__restrict__ list, const uint32_t *__restrict__ count,
                                  int64_t cap, const int32_t *__restrict__ key,
-                                 uint32_t *__restrict__ offsets, FixEntry *__restrict__ out)
+                                 uint32_t *__restrict__ counts, FixEntry *__restrict__ out)
 {
-    __shared__ uint32_t hist[256], base[256];
+    __shared__ uint32_t hist[256], base[256], start[256];
+    bucket_starts(counts, start);
+    uint32_t *cursor = counts + kBuckets;
     const int64_t n = (int64_t)*count < cap ? (int64_t)*count : cap;
     for (int64_t t0 = (int64_t)blockIdx.x * blockDim.x; t0 < n; t0 += (int64_t)gridDim.x * blockDim.x) {
         const int64_t t = t0 + threadIdx.x;
@@ -1130,7 +1161,8 @@ __global__ void fix_place_kernel(const FixEntry *__restrict__ list, const uint32
         const int b = t < n ? key[t] : -1;
         const uint32_t r = b >= 0 ? atomicAdd(hist + b, 1u) : 0u;
         __syncthreads();
-        if (hist[threadIdx.x]) base[threadIdx.x] = atomicAdd(offsets + threadIdx.x, hist[threadIdx.x]);
+        if (hist[threadIdx.x])
+            base[threadIdx.x] = start[threadIdx.x] + atomicAdd(cursor + threadIdx.x, hist[threadIdx.x]);
         __syncthreads();
         if (b >= 0) out[base[b] + r] = list[t];
         __syncthreads();
@@ -1148,7 +1180,6 @@ hipError_t launch_fix_order(const TraceJob *jobs_dev, const FixEntry *list, cons
     hipLaunchKernelGGL(fill_counts_kernel, dim3(1), dim3(256), 0, s, counts);
     hipLaunchKernelGGL(fix_key_kernel, dim3((unsigned)b), dim3(256), 0, s, jobs_dev, list, count, cap,
                        key, counts);
-    hipLaunchKernelGGL(tile_scan_kernel, dim3(1), dim3(64), 0, s, counts);
     hipLaunchKernelGGL(fix_place_kernel, dim3((unsigned)b), dim3(256), 0, s, list, count, cap, key,
                        counts, out);
     return hipGetLastError();
