@@ -463,6 +463,20 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
     for (int i = 0; i < ns; i++)
         live_lines += W[i].nlines * (specs[i].kind == SPEC_PLANE && plane_on_face(specs[i].pl, *specs[i].f) ? 1 : 2);
     const bool ordered = live_lines > kLanes || P.waves_per_cu > 0;
+    // Four lanes to a half line (trace_quad.hip) up to here. The longer the lines, the
+    // later the chip is full enough for one lane to a line to catch up; past 131072 the
+    // eight waves a SIMD that the quads then need no longer fit beside each other. The
+    // trace with one lane over that with four, by live half lines (plane, FP32 / FP64,
+    // interior cut and voxel map of a few random fields):
+    //     64^3           50176 1.08 / 1.23 / 1.10 / 1.10,  92416 1.01 / 1.10 / 1.08 / 0.98,
+    //                   129600 0.92 / 0.98 / 1.01 / 0.89
+    //     256 x 256 x 128  the same three: 1.16 / 1.22 / 1.15 / 1.16,
+    //                   1.15 / 1.33 / 1.15 / 1.05, 1.05 / 1.21 / 1.15 / 1.01
+    // and at 262144 on stretched and Method II planes of 256-node grids 0.89 / 0.92.
+    int64_t longest = 0;
+    for (int i = 0; i < ns; i++)
+        for (int a = 0; a < 3; a++) longest = std::max<int64_t>(longest, specs[i].f->n[a]);
+    const int64_t few_lines = std::min<int64_t>(131072, 65536 + 256 * longest);
     // job table
     std::vector<TraceJob> jobs(njobs);
     int64_t items = 0;
@@ -613,6 +627,7 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
     if (xcd) tp.xcd_ctr = (unsigned long long *)(ws + off_xctr);
     tp.stats = bwd ? nullptr : (unsigned long long *)P.stats;
     tp.static_items = items;
+    tp.few = live_lines <= few_lines;
     if (bwd) {
         tp.tape = (Ckpt *)(ws + off_tape);
         tp.pool_ctr = (unsigned long long *)(ws + off_ctr + 128);

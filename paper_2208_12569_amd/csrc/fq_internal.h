@@ -124,6 +124,8 @@ struct TraceParams {
     int32_t want_tw;
     int32_t njobs;
     int64_t static_items;          // queue items of the main jobs (before the rotated ones)
+    int64_t few;                   // 1 if the main pass takes four lanes to a half line
+    int64_t least;                 // list mode: the kernel runs only if the list is longer
     int32_t dynamic_last;          // 1 if rotated-S0 jobs follow the main jobs: their item
                                    // ranges and the queue's size (*total_dev) are set on
                                    // the device once the classify passes have counted them
@@ -205,6 +207,11 @@ hipError_t launch_store_job(const TraceJob &j, TraceJob *dst, hipStream_t s);
 hipError_t launch_trace(int prec, int store, int twm, const TraceJob *jobs_dev,
                         const TraceParams &tp, unsigned long long *counter, int block,
                         int waves_per_cu, hipStream_t s);
+// The same with four lanes to a half line (trace_quad.hip), if the queue holds at most
+// `most` items (else the kernel ends at once).
+hipError_t launch_trace_quad(bool f64, bool s64, int twm, const TraceJob *jobs_dev, const TraceParams &tp,
+                             unsigned long long *counter, int64_t most, int ncu, int waves_per_cu,
+                             hipStream_t s);
 // Order n items longest first: key (n values, 0..255 = longest; overwritten with the
 // bucket), counts (256), order (n: the item indices in queue order) are workspace.
 hipError_t launch_bucket_order(int64_t n, int32_t *key, uint32_t *counts, int32_t *order,

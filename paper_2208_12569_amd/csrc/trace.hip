@@ -126,6 +126,7 @@ __global__ __launch_bounds__(256, (waves_per_simd<T, TWM, M2, CYL>())) void trac
         total = *tp.total_dev;  // with the rotated-S0 jobs, sized on the device
     }
 
+    if (tp.list && total <= tp.least) return;  // traced with four lanes to a line
     // Few items: the waves that have none to take end at once. Waves are ranked across the
     // blocks first, so that those that stay sit on different CUs: the four of a block
     // would share one CU's gather path (a 17 000-line FP64 pass is a fifth slower so).
@@ -1035,6 +1036,9 @@ hipError_t launch_bucket_order(int64_t n, int32_t *key, uint32_t *counts, int32_
 }
 
 namespace {
+// longest re-trace list that is traced with four lanes to a half line (see launch_trace)
+constexpr int64_t kFewList = 131072;
+
 // FP32 arithmetic reads FP32 records, FP64 arithmetic either; the adjoint's forward pass
 // (tape) the records of its own type. Stretched grids take the multi-job kernels, which
 // carry their per-cell scales, except in the adjoint's single-job pass, which does too.
@@ -1080,6 +1084,25 @@ hipError_t launch_trace(int prec, int store, int twm, const TraceJob *jobs_dev,
         if (twm == 3 && !f64) return hipErrorInvalidValue;
         fn = kernel_for<false>(f64, s64, one && !tp.stretched && !tp.cyl, twm, tp);
     }
+    TraceParams p = tp;
+    p.least = 0;
+    if (!tp.tape && !tp.cyl && tp.scheme == SCH_RKF45) {
+        if (!tp.list) {
+            if (tp.few)
+                return launch_trace_quad(f64, s64, twm, jobs_dev, tp, counter, INT64_MAX, ncu, waves_per_cu, s);
+        } else {
+            // Re-trace lists, whose lengths are on the device: one of the two kernels finds
+            // nothing to do. Up to kFewList halves four lanes to a line (65536: the list of a
+            // 1024 x 1024 plane and of a cut would go the other way, 4530 and 1396 us for
+            // 4457 and 1224; 524288 the same within noise; without end a voxel map's trace
+            // 178.0 ms for 175.0). The half lines still on their way at the end of the FP32
+            // pass are few by nature.
+            const hipError_t e = launch_trace_quad(f64, s64, twm, jobs_dev, tp, counter,
+                                                   tp.list_rev ? INT64_MAX : kFewList, ncu, waves_per_cu, s);
+            if (e != hipSuccess || tp.list_rev) return e;
+            p.least = kFewList;
+        }
+    }
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, block, 0) != hipSuccess) per_cu = 0;
     if (per_cu <= 0) per_cu = 1;
@@ -1088,7 +1111,6 @@ hipError_t launch_trace(int prec, int store, int twm, const TraceJob *jobs_dev,
         if (want < per_cu) per_cu = want;
         if (per_cu < 1) per_cu = 1;
     }
-    TraceParams p = tp;
     void *args[3] = {&jobs_dev, &p, &counter};
     return hipLaunchKernel(fn, dim3((unsigned)(per_cu * ncu)), dim3((unsigned)block), args, 0, s);
 }
