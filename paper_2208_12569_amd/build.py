@@ -16,7 +16,7 @@ LIB = os.path.join(HERE, "libfastqsl.so")
 GATHER_LIB = os.path.join(HERE, "libfqgather.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
 
-SOURCES = ["api.cpp", "prep.hip", "trace.hip", "trace_quad.hip", "stencil.hip", "adjoint.hip", "static_ws.hip"]
+SOURCES = ["api.cpp", "prep.hip", "trace.hip", "trace_quad.hip", "stencil.hip", "adjoint.hip", "adjoint_quad.hip", "static_ws.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

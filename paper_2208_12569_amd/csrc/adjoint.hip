@@ -20,6 +20,7 @@
 // All of it is FP64.
 #include <math.h>
 
+#include "adjoint_dev.h"
 #include "fq_internal.h"
 #include "stencil_dev.h"
 #include "trace_core.h"
@@ -30,6 +31,7 @@ namespace {
 
 using namespace dev;
 using namespace sten;
+using namespace adj;
 
 // ----------------------------------------------------------------------------------
 // Trilinear weights of the caller's planes at a physical point (the cell choice of
@@ -299,20 +301,6 @@ __global__ __launch_bounds__(256) void map_backward_kernel(MapJob m, const doubl
 // ----------------------------------------------------------------------------------
 // Discrete adjoint of one accepted Runge-Kutta step (FP64).
 
-// value and gradient (local coordinates) of P(u,v,w) in monomial form
-template <typename T>
-__device__ __forceinline__ void poly_grad(const T c[8], T u, T v, T w, T g[3])
-{
-    g[0] = c[1] + c[4] * v + c[5] * w + c[7] * v * w;
-    g[1] = c[2] + c[4] * u + c[6] * w + c[7] * u * w;
-    g[2] = c[3] + c[5] * u + c[6] * v + c[7] * u * v;
-}
-
-template <typename T> __device__ __forceinline__ T tri_w(int q, T u, T v, T w)
-{
-    return ((q & 1) ? u : T(1) - u) * ((q & 2) ? v : T(1) - v) * ((q & 4) ? w : T(1) - w);
-}
-
 // The tableaux the forward step uses, by Scheme: Fehlberg 4(5) with its fifth-order
 // weights; classic RK4; Kutta's 3/8 rule (the two RK4 rules use stages 0-3).
 __constant__ double kA[3][6][5] = {
@@ -490,19 +478,6 @@ __device__ void step_adjoint(const T cb[3][8], const T cj[3][8], const StepRec &
     if (ax >= 0 && !onbox) ln[ax] -= dH;  // H = face - p_axis
     for (int a = 0; a < 3; a++) lam[a] = ln[a];
 }
-
-// Captures the accepted step of a replayed trial.
-struct Capture {
-    int *axis;
-    double *H;
-    int *clamp;
-    template <typename T> __device__ __forceinline__ void accepted(int a, T h, int cl) const
-    {
-        *axis = a;
-        *H = (double)h;
-        *clamp = cl;
-    }
-};
 
 template <typename T, bool TW>
 __device__ void flush_cell(double *gnode, int64_t nn, int nx, int ny, int c0, int c1, int c2,
@@ -915,8 +890,10 @@ void launch_bwd_s(int store, int want_tw, const TraceJob *job_dev, const BwdPara
 {
     const dim3 grid((unsigned)((bp.nslots + 63) / 64)), blk(64);
     if (store == FQ_DT_F64) {
-        if (want_tw) hipLaunchKernelGGL((trace_backward_kernel<double, double, true, SCH>), grid, blk, 0, s, job_dev, bp);
-        else hipLaunchKernelGGL((trace_backward_kernel<double, double, false, SCH>), grid, blk, 0, s, job_dev, bp);
+        if constexpr (SCH != SCH_RKF45) {
+            if (want_tw) hipLaunchKernelGGL((trace_backward_kernel<double, double, true, SCH>), grid, blk, 0, s, job_dev, bp);
+            else hipLaunchKernelGGL((trace_backward_kernel<double, double, false, SCH>), grid, blk, 0, s, job_dev, bp);
+        }
     } else {
         if (want_tw) hipLaunchKernelGGL((trace_backward_kernel<float, float, true, SCH>), grid, blk, 0, s, job_dev, bp);
         else hipLaunchKernelGGL((trace_backward_kernel<float, float, false, SCH>), grid, blk, 0, s, job_dev, bp);
@@ -927,6 +904,10 @@ void launch_bwd_s(int store, int want_tw, const TraceJob *job_dev, const BwdPara
 hipError_t launch_trace_backward(int store, int want_tw, const TraceJob *job_dev,
                                  const BwdParams &bp, hipStream_t s)
 {
+    // FP64 adaptive steps with four lanes to a half line. FP32 ones stay with one lane: the
+    // gradient sums of a cell are FP32 there, and summing them in another order moves the
+    // gradient by 2e-6 of its size.
+    if (bp.scheme == SCH_RKF45 && store == FQ_DT_F64) return launch_trace_backward_quad(want_tw, job_dev, bp, s);
     if (bp.scheme == SCH_RKF45) launch_bwd_s<SCH_RKF45>(store, want_tw, job_dev, bp, s);
     else if (bp.scheme == SCH_RK4) launch_bwd_s<SCH_RK4>(store, want_tw, job_dev, bp, s);
     else if (bp.scheme == SCH_RK4_38) launch_bwd_s<SCH_RK4_38>(store, want_tw, job_dev, bp, s);

@@ -165,7 +165,7 @@ struct BwdParams {
     const double *lam_tw;          // per half: dL/d(Tw of the half)
     double *gnode;                 // 6 planes over the nodes: dL/d(Bx, By, Bz, Jx, Jy, Jz)
     StepRec *buf;                  // nslots * seg replay records
-    int64_t nslots;                // lanes of the reverse kernel
+    int64_t nslots;                // half lines in the reverse kernel at once
     unsigned long long *counter;   // queue
     const int32_t *order;          // the half lines in queue order (longest first)
     unsigned long long *stats;     // optional: halves, steps, replay mismatches, dropped halves
@@ -274,9 +274,12 @@ hipError_t launch_bwd_order(const int32_t *tape_acc, int64_t nhalves, int32_t *k
                             uint32_t *counts, int32_t *order, hipStream_t s);
 hipError_t launch_trace_backward(int store, int want_tw, const TraceJob *job_dev,
                                  const BwdParams &bp, hipStream_t s);
+// RKF45's in FP64, with four lanes to a half line (adjoint_quad.hip)
+hipError_t launch_trace_backward_quad(int want_tw, const TraceJob *job_dev, const BwdParams &bp,
+                                      hipStream_t s);
 hipError_t launch_grad_planes(const fq_field &f, const double *gnode, int want_tw,
                               double *const gb[3], hipStream_t s);
-constexpr int64_t kBwdSlots = 32768;  // lanes of the reverse kernel
+constexpr int64_t kBwdSlots = 32768;  // half lines in the reverse kernel at once
 
 hipError_t launch_classify(const MapJob &m, int32_t *rot_index, RotEntry *rot,
                            uint32_t *rot_count, int64_t rot_capacity, hipStream_t s);

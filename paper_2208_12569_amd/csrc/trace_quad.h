@@ -136,10 +136,11 @@ __device__ __forceinline__ void tangent(const T cb[8], const T Y[3], const Line<
     }
 }
 
-// One trial step (RKF45): lane_iterate's cases and results.
-template <typename T, bool TW, bool M2>
+// One trial step (RKF45): lane_iterate's cases and results, its event sink too.
+template <typename T, bool TW, bool M2, typename EV = NoEvents>
 __device__ __forceinline__ void iterate(Line<T> &L, const T cb[8], const T cj[8], const Const<T> &K,
-                                        int &fin_st, int &fin_face, bool &need_load, unsigned &n_acc)
+                                        int &fin_st, int &fin_face, bool &need_load, unsigned &n_acc,
+                                        const EV &ev = EV{})
 {
 // products and sums round as written (a fused one is an fma_)
 #pragma clang fp contract(off)
@@ -340,11 +341,13 @@ __device__ __forceinline__ void iterate(Line<T> &L, const T cb[8], const T cj[8]
             L.len += (double)(H * slen);
         }
         n_acc++;
+        int cl = 0;
         if (G & 7) {
-            int cl = 0;
             if (past) moved = carry(L.cell, L.p, L.n, cl, 1);
             moved = any(moved);
+            cl = any(cl << L.c);
         }
+        ev.accepted(land ? lax : -1, H, cl);
     }
     // cross the face reached: the next cell, or the end of the line
     const bool x = live & cross, xl = acc & land;

@@ -147,3 +147,36 @@ def test_prep_at_row_and_wave_edges(fq, n, prec):
         r = fq.q2d(_dev(B), g, pl, fq.Params(precision=prec), want_lines=True)
         torch.cuda.synchronize()
         compare_maps(r, oracle.q2d(B, g, pl, {"tol": 1e-10}), f"prep {n}")
+
+
+@pytest.mark.parametrize("nu,nv", [(2, 2), (4, 4), (17, 3), (40, 21)])
+@pytest.mark.parametrize("prec", [F32X, F64], ids=["f32x", "f64"])
+def test_reverse_of_few_lines(fq, nu, nv, prec):
+    """The reverse pass with four lanes to a half line, segments of 1, 5 and 32 steps: every
+    replay finds its next checkpoint, and in FP64 the gradient does not depend on the
+    segments (sums in another order, so 1e-12 of the largest value)."""
+    import torch
+
+    rng = np.random.default_rng(nu)
+    for stretched in (False, True):
+        g = _grid(stretched)
+        B = _field(g, 11, np.float64)
+        for z in (0.0, 0.21):
+            pl = Plane((0.23, 0.31, z), (1, 0, 0), (0, 1, 0), nu, nv, 0.4 / nu, 0.3 / nv)
+            dq = torch.from_numpy(rng.normal(size=(nv, nu))).cuda()
+            dtw = torch.from_numpy(rng.normal(size=(nv, nu))).cuda()
+            ref = None
+            for seg in (32, 5, 1):
+                _say(f"reverse {nu}x{nv} z {z}, precision {prec}, stretched {stretched}, segments of {seg}")
+                st = torch.zeros(5, dtype=torch.int64, device="cuda")
+                r = fq.backward(B, g, pl, fq.Params(precision=prec, stats=st, tape_steps=1000),
+                                segment=seg, dq=dq, dtw=dtw)
+                torch.cuda.synchronize()
+                gb = to_np(r)
+                assert int(st[0]) > 0 and int(st[2]) == 0 and int(st[3]) == 0, st
+                assert np.all(np.isfinite(gb))
+                if ref is None:
+                    ref = gb
+                if prec == F64:
+                    lim = 1e-12 * np.abs(ref).max()
+                    assert np.abs(gb - ref).max() <= lim, (seg, np.abs(gb - ref).max(), lim)
