@@ -169,7 +169,7 @@ __device__ __forceinline__ void push_line(const MapJob &m, int64_t l, bool swapp
 }
 
 __device__ void bn_adj(const MapJob &m, const double r[3], int comp, double gbn, double eb[3],
-                       double *gnode, int64_t nn)
+                       double *gnode)
 {
     Tri t;
     tri_of(m, r, t);
@@ -178,7 +178,7 @@ __device__ void bn_adj(const MapJob &m, const double r[3], int comp, double gbn,
         grad_comp(m, t, comp, g);
         for (int a = 0; a < 3; a++) eb[a] += gbn * g[a];
     }
-    for (int q = 0; q < 8; q++) atomicAdd(gnode + comp * nn + t.node[q], gbn * t.w[q]);
+    for (int q = 0; q < 8; q++) atomicAdd(gnode + t.node[q] * m.gstride + comp, gbn * t.w[q]);
 }
 
 __global__ __launch_bounds__(256) void map_backward_kernel(MapJob m, const double *__restrict__ dq,
@@ -189,7 +189,6 @@ __global__ __launch_bounds__(256) void map_backward_kernel(MapJob m, const doubl
 {
     // a 3-D map's layers each take the plane's stencil, with neighbours in the layer
     const int64_t lay = m.nu * m.nv, np = lay * m.nlayers;
-    const int64_t nn = (int64_t)m.n[0] * m.n[1] * m.n[2];
     for (int64_t pt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; pt < np;
          pt += (int64_t)gridDim.x * blockDim.x) {
         const int64_t k = pt / lay, r2 = pt - k * lay, j = r2 / m.nu, i = r2 - j * m.nu;
@@ -273,13 +272,13 @@ __global__ __launch_bounds__(256) void map_backward_kernel(MapJob m, const doubl
             axis_adj(ry, c, ym, yp, dy, d1b, d2b, ca, yma, ypa);
         }
         // the normal fields: Q ~ |Bn1 Bn2| / Bn0^2
-        bn_adj(m, c.e1, a1, gq * Q / bn1, ca.e1, gnode, nn);
-        bn_adj(m, c.e2, a2, gq * Q / bn2, ca.e2, gnode, nn);
+        bn_adj(m, c.e1, a1, gq * Q / bn1, ca.e1, gnode);
+        bn_adj(m, c.e2, a2, gq * Q / bn2, ca.e2, gnode);
         const double gb0 = -2.0 * gq * Q / bn0;
         // Bn0 = n.B0, or |B0| on a rotated S0 (d|B0| / dB0 = B0 / |B0|)
         for (int comp = 0; comp < 3; comp++) {
             const double w = rot ? B0[comp] / bn0 : m.normal[comp];
-            if (w != 0.0) bn_adj(m, r0, comp, gb0 * w, nullptr, gnode, nn);
+            if (w != 0.0) bn_adj(m, r0, comp, gb0 * w, nullptr, gnode);
         }
         push_line(m, pt, c.swapped, ca, lam_end);
         if (rot) {
@@ -480,18 +479,17 @@ __device__ void step_adjoint(const T cb[3][8], const T cj[3][8], const StepRec &
 }
 
 template <typename T, bool TW>
-__device__ void flush_cell(double *gnode, int64_t nn, int nx, int ny, int c0, int c1, int c2,
-                           T gB[3][8], T gJ[3][8])
+__device__ void flush_cell(double *gnode, int nx, int ny, int c0, int c1, int c2, T gB[3][8], T gJ[3][8])
 {
     const int64_t sy = nx, sz = (int64_t)nx * ny;
     const int64_t base = (int64_t)c2 * sz + (int64_t)c1 * sy + c0;
     for (int q = 0; q < 8; q++) {
         const int64_t o = base + (q & 1) + ((q >> 1) & 1) * sy + ((q >> 2) & 1) * sz;
         for (int c = 0; c < 3; c++) {
-            if (gB[c][q] != T(0)) atomicAdd(gnode + c * nn + o, (double)gB[c][q]);
+            if (gB[c][q] != T(0)) atomicAdd(gnode + o * (TW ? 6 : 3) + c, (double)gB[c][q]);
             gB[c][q] = T(0);
             if (TW) {
-                if (gJ[c][q] != T(0)) atomicAdd(gnode + (3 + c) * nn + o, (double)gJ[c][q]);
+                if (gJ[c][q] != T(0)) atomicAdd(gnode + o * 6 + 3 + c, (double)gJ[c][q]);
                 gJ[c][q] = T(0);
             }
         }
@@ -529,7 +527,6 @@ __global__ __launch_bounds__(64) void trace_backward_kernel(const TraceJob *__re
         K.ry = (T)(dref * J.iw[1][c1]);
         K.rz = (T)(dref * J.iw[2][c2]);
     };
-    const int64_t nn = (int64_t)K.nx * K.ny * K.nz;
     unsigned long long n_half = 0, n_steps = 0, n_bad = 0, n_drop = 0;
     T cb[3][8], cj[3][8], gB[3][8], gJ[3][8];
     for (int c = 0; c < 3; c++)
@@ -652,7 +649,7 @@ __global__ __launch_bounds__(64) void trace_backward_kernel(const TraceJob *__re
                 for (int r = nrec - 1; r >= 0; r--) {
                     const StepRec sr = buf[r];
                     if (sr.c0 != cc0 || sr.c1 != cc1 || sr.c2 != cc2) {
-                        if (cc0 >= 0) flush_cell<T, TW>(bp.gnode, nn, K.nx, K.ny, cc0, cc1, cc2, gB, gJ);
+                        if (cc0 >= 0) flush_cell<T, TW>(bp.gnode, K.nx, K.ny, cc0, cc1, cc2, gB, gJ);
                         cc0 = sr.c0, cc1 = sr.c1, cc2 = sr.c2;
                         load_cell<T, S, TW>(J.nodes, K.nx, K.ny, cc0, cc1, cc2, cb, cj);
                         cell_scales(cc0, cc1, cc2);
@@ -661,7 +658,7 @@ __global__ __launch_bounds__(64) void trace_backward_kernel(const TraceJob *__re
                     step_adjoint<T, TW, SCH>(cb, cj, sr, K, sgn, endb, lam, ltw, gB, gJ);
                     n_steps++;
                 }
-                if (cc0 >= 0) flush_cell<T, TW>(bp.gnode, nn, K.nx, K.ny, cc0, cc1, cc2, gB, gJ);
+                if (cc0 >= 0) flush_cell<T, TW>(bp.gnode, K.nx, K.ny, cc0, cc1, cc2, gB, gJ);
                 if (ck == 0 && rj == 1 && bp.lam_seed) {
                     // a rotated-S0 line's adjoint at its seed, which depends on B0 (its
                     // offset along U or V): local units -> physical
@@ -721,7 +718,8 @@ __device__ __forceinline__ double dcoef_s(int m, int n, int N, const double *x)
     return 0.0;
 }
 
-// (D_axis)^T g at node (i, j, k): sum over the nodes m whose difference uses it
+// (D_axis)^T g at node (i, j, k): sum over the nodes m whose difference uses it; g is one
+// of the six values of a node
 // (x: the axis's node coordinates on a stretched axis, else NULL)
 __device__ double dT(const double *g, int axis, int i, int j, int k, int nx, int ny, int nz,
                      double ih, const double *x)
@@ -735,7 +733,7 @@ __device__ double dT(const double *g, int axis, int i, int j, int k, int nx, int
     for (int m = lo; m <= hi; m++) {
         if (m < 0 || m >= N) continue;
         const double c = x ? dcoef_s(m, n, N, x) : dcoef(m, n, N, ih);
-        if (c != 0.0) acc += c * g[q + (int64_t)(m - n) * stride];
+        if (c != 0.0) acc += c * g[6 * (q + (int64_t)(m - n) * stride)];
     }
     return acc;
 }
@@ -748,12 +746,12 @@ __global__ void grad_planes_kernel(int nx, int ny, int nz, double ihx, double ih
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int j = blockIdx.y, k = blockIdx.z;
     if (i >= nx) return;
-    const int64_t nn = (int64_t)nx * ny * nz;
     const int64_t q = ((int64_t)k * ny + j) * nx + i;
-    double bx = gnode[q], by = gnode[nn + q], bz = gnode[2 * nn + q];
+    const double *gq = gnode + (want_tw ? 6 : 3) * q;
+    double bx = gq[0], by = gq[1], bz = gq[2];
     if (want_tw) {
         // J = (dBz/dy - dBy/dz, dBx/dz - dBz/dx, dBy/dx - dBx/dy)
-        const double *gjx = gnode + 3 * nn, *gjy = gnode + 4 * nn, *gjz = gnode + 5 * nn;
+        const double *gjx = gnode + 3, *gjy = gnode + 4, *gjz = gnode + 5;
         bx += dT(gjy, 2, i, j, k, nx, ny, nz, ihz, cz) - dT(gjz, 1, i, j, k, nx, ny, nz, ihy, cy);
         by += dT(gjz, 0, i, j, k, nx, ny, nz, ihx, cx) - dT(gjx, 2, i, j, k, nx, ny, nz, ihz, cz);
         bz += dT(gjx, 1, i, j, k, nx, ny, nz, ihy, cy) - dT(gjy, 0, i, j, k, nx, ny, nz, ihx, cx);
@@ -788,7 +786,6 @@ __global__ void rot_seed_kernel(MapJob m, const RotEntry *__restrict__ rot,
                                 const uint32_t *__restrict__ rot_count, int64_t cap,
                                 const double *__restrict__ lam_seed, double *gnode)
 {
-    const int64_t nn = (int64_t)m.n[0] * m.n[1] * m.n[2];
     int64_t cnt = (int64_t)*rot_count;
     if (cnt > cap) cnt = cap;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < cnt;
@@ -839,7 +836,7 @@ __global__ void rot_seed_kernel(MapJob m, const RotEntry *__restrict__ rot,
         for (int c = 0; c < 3; c++) {
             const double gB = (gb[c] - b[c] * bb) / bm;
             if (gB == 0.0) continue;
-            for (int q = 0; q < 8; q++) atomicAdd(gnode + c * nn + t.node[q], gB * t.w[q]);
+            for (int q = 0; q < 8; q++) atomicAdd(gnode + t.node[q] * m.gstride + c, gB * t.w[q]);
         }
     }
 }

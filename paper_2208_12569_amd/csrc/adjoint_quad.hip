@@ -3,11 +3,13 @@
 // the adjoint and of the cell's gradient sums.
 //
 // Bound by instruction issue: about 1500 vector instructions for the adjoint of an
-// accepted step and 900 for each trial of its replay, with two waves per SIMD; the atomic
-// adds of the cells' sums to the nodes are a third of its time on top. One lane to a line
+// accepted step and 900 for each trial of its replay, with two waves per SIMD. The atomic
+// adds of the cells' sums to the nodes cost 1.9 ms of 5.7 while each component had a plane
+// of its own, and 0.5 ms since a node's values lie side by side, where the three lanes of a
+// half line add to one cache line. One lane to a line
 // needs 510 registers, so one wave per SIMD, and the replay buffer, sized by half lines,
 // gave it 512 waves for 1024 SIMDs; four lanes make that 2048 waves at two per SIMD. The
-// map, loss and gradient of a 256 x 256 plane on a 128x128x96 FP64 field 9.43 -> 7.68 ms.
+// map, loss and gradient of a 256 x 256 plane on a 128x128x96 field in FP64 9.43 -> 7.68 -> 6.24 ms.
 #include <math.h>
 
 #include "adjoint_dev.h"
@@ -159,18 +161,19 @@ __device__ __forceinline__ void step_adjoint(const T cb[8], const T cj[8], const
 
 // This lane's component of the cell's sums to the nodes.
 template <typename T, bool TW>
-__device__ __forceinline__ void flush_cell(double *gnode, int64_t nn, int nx, int ny, int c, int cell, T gB[8], T gJ[8])
+__device__ __forceinline__ void flush_cell(double *gnode, int nx, int ny, int c, int cell, T gB[8], T gJ[8])
 {
     const int c0 = from<0>(cell), c1 = from<1>(cell), c2 = from<2>(cell);
-    const int64_t sy = nx, sz = (int64_t)nx * ny;
-    double *g = gnode + (int64_t)c * nn + (int64_t)c2 * sz + (int64_t)c1 * sy + c0;
+    constexpr int kNode = TW ? 6 : 3;
+    const int64_t sy = (int64_t)nx * kNode, sz = sy * ny;
+    double *g = gnode + (c2 * sz + c1 * sy + c0 * kNode + c);
 #pragma unroll
     for (int q = 0; q < 8; q++) {
-        double *o = g + (q & 1) + ((q >> 1) & 1) * sy + ((q >> 2) & 1) * sz;
+        double *o = g + (q & 1) * kNode + ((q >> 1) & 1) * sy + ((q >> 2) & 1) * sz;
         if (c < 3 && gB[q] != T(0)) atomicAdd(o, (double)gB[q]);
         gB[q] = T(0);
         if (TW) {
-            if (c < 3 && gJ[q] != T(0)) atomicAdd(o + 3 * nn, (double)gJ[q]);
+            if (c < 3 && gJ[q] != T(0)) atomicAdd(o + 3, (double)gJ[q]);
             gJ[q] = T(0);
         }
     }
@@ -185,7 +188,6 @@ __global__ __launch_bounds__(64, 2) void trace_backward_quad_kernel(const TraceJ
     if (slot >= bp.nslots) return;
     QuadRec *buf = (QuadRec *)(bp.buf + slot * bp.seg);
     const int nx = J.n[0], ny = J.n[1];
-    const int64_t nn = (int64_t)nx * ny * J.n[2];
     quad::Const<T> K;
     K.twk = (T)J.twk;
     K.bnull2 = (T)((double)Num<T>::null_rel * (double)(*J.bmax2));
@@ -326,7 +328,7 @@ __global__ __launch_bounds__(64, 2) void trace_backward_quad_kernel(const TraceJ
                     const int code = from<3>(w), cell = c < 3 ? w : 0;
                     if (r > 0) v = buf[r - 1].v[c], w = buf[r - 1].w[c];
                     if (any(cell != L.cell)) {
-                        if (r != nrec - 1) flush_cell<T, TW>(bp.gnode, nn, nx, ny, c, L.cell, gB, gJ);
+                        if (r != nrec - 1) flush_cell<T, TW>(bp.gnode, nx, ny, c, L.cell, gB, gJ);
                         L.cell = cell;
                         fetch();
                     }
@@ -334,7 +336,7 @@ __global__ __launch_bounds__(64, 2) void trace_backward_quad_kernel(const TraceJ
                     step_adjoint<T, TW>(cb, cj, L, K.twk, p, H, (code & 3) - 1, code >> 2, endb, lam, ltw, gB, gJ);
                     n_steps++;
                 }
-                if (nrec > 0) flush_cell<T, TW>(bp.gnode, nn, nx, ny, c, L.cell, gB, gJ);
+                if (nrec > 0) flush_cell<T, TW>(bp.gnode, nx, ny, c, L.cell, gB, gJ);
                 if (ck == 0 && rj == 1 && bp.lam_seed && c < 3) {
                     // a rotated-S0 line's adjoint at its seed, which depends on B0 (its
                     // offset along U or V): local units -> physical

@@ -439,6 +439,7 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
         memset(&m, 0, sizeof m);
         set_map_geometry(s, m);
         m.edge_eps = P.edge_eps;
+        m.gstride = P.want_tw ? 6 : 3;
         m.rec = recs_at(ws, w.end, w.tw, w.len, w.face, w.st);
         if (m2) m.rec.uv = (double *)(ws + w.uv);
         m.nlines = w.nlines;

@@ -163,7 +163,9 @@ struct BwdParams {
     int64_t nhalves;               // 2 * nlines
     const double *lam_end;         // per half: dL/d(end point), 3 doubles
     const double *lam_tw;          // per half: dL/d(Tw of the half)
-    double *gnode;                 // 6 planes over the nodes: dL/d(Bx, By, Bz, Jx, Jy, Jz)
+    // per node dL/d(Bx, By, Bz) and, with twist, dL/d(Jx, Jy, Jz) side by side: the lanes of
+    // a half line add to one or two cache lines instead of six
+    double *gnode;
     StepRec *buf;                  // nslots * seg replay records
     int64_t nslots;                // half lines in the reverse kernel at once
     unsigned long long *counter;   // queue
@@ -244,6 +246,7 @@ struct MapJob {
     int32_t n[3];
     double origin[3], spacing[3];
     const double *coord[3];  // node coordinates of stretched axes (NULL = uniform axis)
+    int64_t gstride;             // adjoint: doubles per node in gnode (below)
     int64_t nu, nv, nlayers;     // points per layer = nu*nv
     double d0, d1;               // seed spacing along the two S0 axes
     double normal[3];            // S0 normal
