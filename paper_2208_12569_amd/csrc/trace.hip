@@ -26,6 +26,7 @@
 //    (one atomic per wave via a ballot), so waves never idle on their longest line.
 //    Queue items follow 64-seed tiles, so the lanes of a wave start on neighbouring
 //    seeds and read neighbouring cells.
+// Launches of few lines take four lanes to a half line instead (trace_quad.hip).
 #include "fq_internal.h"
 #include "trace_core.h"
 #include "trace_dev.h"
@@ -81,7 +82,8 @@ template <typename T> constexpr int refill_min() { return sizeof(T) == 4 ? 24 : 
 // TWM: 0 = no twist (narrow records), 1 = twist, 2 = positions only on wide records
 // (the FP64 re-trace, which keeps the twist of the first pass); 3 = as 2, held to
 // three waves per SIMD (168 VGPRs, 52-64 bytes of spills per lane) for calls
-// that share the GPU with other maps in flight: its waves then leave room for theirs.
+// that share the GPU with other maps in flight: its waves then leave room for theirs
+// (lists that four lanes to a line trace run three waves per SIMD in any call).
 // SCH: the integration scheme (Scheme in trace_core.h), the adjoint's forward pass
 // (TAPE) included. M2: Method II, the tangent vectors U, V ride along (their
 // end values go to the records' uv array). CYL: jobs may run inside a cylinder.
@@ -1086,7 +1088,7 @@ hipError_t launch_trace(int prec, int store, int twm, const TraceJob *jobs_dev,
     }
     TraceParams p = tp;
     p.least = 0;
-    if (!tp.tape && !tp.cyl && tp.scheme == SCH_RKF45) {
+    if (!tp.cyl && tp.scheme == SCH_RKF45) {
         if (!tp.list) {
             if (tp.few)
                 return launch_trace_quad(f64, s64, twm, jobs_dev, tp, counter, INT64_MAX, ncu, waves_per_cu, s);

@@ -1,5 +1,5 @@
 // Tracer with four lanes to a half line, for launches of few lines: RKF45, Method I and
-// II, uniform and stretched grids, any number of jobs (trace.hip has the queue, the
+// II, the adjoint's forward pass, uniform and stretched grids, any number of jobs (trace.hip has the queue, the
 // records and everything else that the two kernels share in meaning; trace_quad.h the
 // step). Results are those of trace_kernel, bit for bit.
 //
@@ -10,7 +10,8 @@
 // look of 16384 lines 1097 -> 761 us, a 128^3 FP64 plane 812 -> 676, an interior cut of
 // 255 x 129 points 1612 -> 1224, 30001 seeds from a list 3352 -> 2895; through the FP64
 // re-trace of an FP32 pass also large calls, a 1024 x 1024 plane 4951 -> 4457, eight in a
-// batch 32.7 -> 27.1 ms.
+// batch 32.7 -> 27.1 ms; the map, loss and gradient of a 256 x 256 plane, whose forward
+// pass this is as well, 6.26 -> 6.12 ms.
 #include "fq_internal.h"
 #include <algorithm>
 #include "trace_quad.h"
@@ -21,9 +22,38 @@ namespace {
 using namespace dev;
 using quad::all3;
 
+// A checkpoint of the adjoint's forward pass (store_ckpt in trace.hip).
+template <typename T> __device__ __forceinline__ bool store_ckpt(const TraceParams &tp, int &last, const quad::Line<T> &L)
+{
+    unsigned long long slot = 0;
+    if (L.c == 0) slot = atomicAdd(tp.pool_ctr, 1ull);
+    slot = (unsigned long long)(unsigned)quad::from<0>((int)slot) |
+           ((unsigned long long)(unsigned)quad::from<0>((int)(slot >> 32)) << 32);
+    if (slot >= (unsigned long long)tp.pool_cap) return false;  // the pool is exhausted
+    const int c0 = quad::from<0>(L.cell), c1 = quad::from<1>(L.cell), c2 = quad::from<2>(L.cell);
+    if (L.c == 0) {
+        Ckpt c;
+        c.p0 = (double)L.P[0];
+        c.p1 = (double)L.P[1];
+        c.p2 = (double)L.P[2];
+        c.h = (double)L.h;
+        c.tol = (double)L.tol;
+        c.c0 = c0;
+        c.c1 = c1;
+        c.c2 = c2;
+        c.force = L.force;
+        c.trials = (int32_t)L.trials;
+        c.prev = last;
+        gptr(tp.tape)[slot] = c;
+    }
+    last = (int)slot;
+    return true;
+}
+
 // TWM as trace_kernel's: 0 no twist (narrow records), 1 twist, 2 positions only on wide
-// records. Runs only if the queue holds at most `most` items.
-template <typename T, typename S, int TWM, bool M2>
+// records. TAPE: the adjoint's forward pass. Runs only if the queue holds at most `most`
+// items.
+template <typename T, typename S, int TWM, bool M2, bool TAPE>
 __global__ __launch_bounds__(256, sizeof(T) == 4 ? (M2 ? 3 : 4) : (M2 ? 2 : 3)) void trace_quad_kernel(
     const TraceJob *__restrict__ jobs, TraceParams tp, unsigned long long *__restrict__ counter, int64_t most)
 {
@@ -56,6 +86,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? (M2 ? 3 : 4) : (M2 ? 2 : 3)) 
     K.max_steps = (uint32_t)(tp.max_steps < 0xfffffffell ? tp.max_steps : 0xfffffffell);
     T cb[8], cj[8];
     unsigned n_trial = 0, n_acc = 0, n_fetch = 0, n_half = 0;
+    int acc_half = 0, nck = 0, last_ck = -1;  // TAPE: steps, checkpoints, the last one's slot
 
     for (;;) {
         int fin_st = -1, fin_face = -1;
@@ -118,6 +149,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? (M2 ? 3 : 4) : (M2 ? 2 : 3)) 
                         L.len = 0.0;
                         L.trials = 0;
                         L.force = -1;
+                        if (TAPE) acc_half = 0, nck = 0, last_ck = -1;
                         bool in = !(str && J.geo->bad);
                         int cell[3] = {0, 0, 0};
                         for (int a = 0; a < 3; a++) {
@@ -199,13 +231,29 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? (M2 ? 3 : 4) : (M2 ? 2 : 3)) 
                     L.u = (c == 0 ? u[0] : (c == 1 ? u[1] : u[2])) * is;
                     L.v = (c == 0 ? v[0] : (c == 1 ? v[1] : v[2])) * is;
                 }
+                if (TAPE) {
+                    if (store_ckpt(tp, last_ck, L)) nck++;
+                    else fin_st = FQ_ST_MAXSTEPS | FQ_ST_NOTAPE;  // no checkpoint space
+                }
             }
         }
 
         // ---- one trial step ---------------------------------------------------------------
         if (jb >= 0 && fin_st < 0) {
             n_trial++;
+            const unsigned acc_before = n_acc;
             quad::iterate<T, TW, M2>(L, cb, cj, K, fin_st, fin_face, need_load, n_acc);
+            if (TAPE && n_acc != acc_before) {
+                acc_half++;
+                if (fin_st < 0 && acc_half % tp.seg == 0) {
+                    if (store_ckpt(tp, last_ck, L)) {
+                        nck++;
+                    } else {
+                        fin_st = FQ_ST_MAXSTEPS | FQ_ST_NOTAPE;  // no checkpoint space
+                        fin_face = -1;
+                    }
+                }
+            }
         }
 
         // ---- write the record of a finished half line -------------------------------------
@@ -236,6 +284,13 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? (M2 ? 3 : 4) : (M2 ? 2 : 3)) 
                 gptr(J.rec.len)[rec] = bad ? NAN : L.len * (str ? dref_s : J.dref);
                 gptr(J.rec.face)[rec] = bad ? (int8_t)-1 : (int8_t)fin_face;
                 gptr(J.rec.st)[rec] = (uint16_t)fin_st;
+                if (TAPE) {
+                    // a rotated-S0 job's halves follow the plane's
+                    const int64_t trec = rec + (jb > 0 ? tp.tape_base1 : 0);
+                    gptr(tp.tape_last)[trec] = last_ck;
+                    gptr(tp.tape_n)[trec] = nck;
+                    gptr(tp.tape_acc)[trec] = acc_half;
+                }
             }
             jb = -1;
             need_load = false;
@@ -259,14 +314,18 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? (M2 ? 3 : 4) : (M2 ? 2 : 3)) 
     }
 }
 
-template <typename T, typename S> const void *pick(int twm, int method)
+template <typename T, typename S> const void *pick(int twm, const TraceParams &tp)
 {
-    if (method == FQ_METHOD_II)
-        return twm == 1 ? (const void *)trace_quad_kernel<T, S, 1, true>
-                        : (const void *)trace_quad_kernel<T, S, 0, true>;
-    return twm == 1   ? (const void *)trace_quad_kernel<T, S, 1, false>
-           : twm == 0 ? (const void *)trace_quad_kernel<T, S, 0, false>
-                      : (const void *)trace_quad_kernel<T, S, 2, false>;
+    if constexpr (sizeof(T) == sizeof(S))
+        if (tp.tape)
+            return twm == 1 ? (const void *)trace_quad_kernel<T, S, 1, false, true>
+                            : (const void *)trace_quad_kernel<T, S, 0, false, true>;
+    if (tp.method == FQ_METHOD_II)
+        return twm == 1 ? (const void *)trace_quad_kernel<T, S, 1, true, false>
+                        : (const void *)trace_quad_kernel<T, S, 0, true, false>;
+    return twm == 1   ? (const void *)trace_quad_kernel<T, S, 1, false, false>
+           : twm == 0 ? (const void *)trace_quad_kernel<T, S, 0, false, false>
+                      : (const void *)trace_quad_kernel<T, S, 2, false, false>;
 }
 
 }  // namespace
@@ -275,8 +334,8 @@ hipError_t launch_trace_quad(bool f64, bool s64, int twm, const TraceJob *jobs_d
                              unsigned long long *counter, int64_t most, int ncu, int waves_per_cu,
                              hipStream_t s)
 {
-    const void *fn = !f64 ? pick<float, float>(twm, tp.method)
-                     : s64 ? pick<double, double>(twm, tp.method) : pick<double, float>(twm, tp.method);
+    const void *fn = !f64 ? pick<float, float>(twm, tp)
+                     : s64 ? pick<double, double>(twm, tp) : pick<double, float>(twm, tp);
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 256, 0) != hipSuccess || per_cu <= 0) per_cu = 1;
     if (waves_per_cu > 0) per_cu = std::max(1, std::min(per_cu, waves_per_cu / 4));
