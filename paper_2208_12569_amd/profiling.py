@@ -22,7 +22,7 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 COPY_BYTES = 1 << 30
-TRACER = "trace_kernel<float, float, 1, true, false, 0, false>"
+TRACER = "trace_kernel<float, float, 1, true, false, 0, false"  # the FP32 pass of one job
 
 
 def kernel_source_sha() -> str:
