@@ -178,7 +178,7 @@ __device__ void bn_adj(const MapJob &m, const double r[3], int comp, double gbn,
         grad_comp(m, t, comp, g);
         for (int a = 0; a < 3; a++) eb[a] += gbn * g[a];
     }
-    for (int q = 0; q < 8; q++) atomicAdd(gnode + t.node[q] * m.gstride + comp, gbn * t.w[q]);
+    for (int q = 0; q < 8; q++) atomicAdd(gnode + t.node[q] * m.gstride + comp * m.gplane, gbn * t.w[q]);
 }
 
 __global__ __launch_bounds__(256) void map_backward_kernel(MapJob m, const double *__restrict__ dq,
@@ -479,17 +479,18 @@ __device__ void step_adjoint(const T cb[3][8], const T cj[3][8], const StepRec &
 }
 
 template <typename T, bool TW>
-__device__ void flush_cell(double *gnode, int nx, int ny, int c0, int c1, int c2, T gB[3][8], T gJ[3][8])
+__device__ void flush_cell(double *gnode, int64_t nn, int nx, int ny, int c0, int c1, int c2,
+                           T gB[3][8], T gJ[3][8])
 {
     const int64_t sy = nx, sz = (int64_t)nx * ny;
     const int64_t base = (int64_t)c2 * sz + (int64_t)c1 * sy + c0;
     for (int q = 0; q < 8; q++) {
         const int64_t o = base + (q & 1) + ((q >> 1) & 1) * sy + ((q >> 2) & 1) * sz;
         for (int c = 0; c < 3; c++) {
-            if (gB[c][q] != T(0)) atomicAdd(gnode + o * (TW ? 6 : 3) + c, (double)gB[c][q]);
+            if (gB[c][q] != T(0)) atomicAdd(gnode + c * nn + o, (double)gB[c][q]);
             gB[c][q] = T(0);
             if (TW) {
-                if (gJ[c][q] != T(0)) atomicAdd(gnode + o * 6 + 3 + c, (double)gJ[c][q]);
+                if (gJ[c][q] != T(0)) atomicAdd(gnode + (3 + c) * nn + o, (double)gJ[c][q]);
                 gJ[c][q] = T(0);
             }
         }
@@ -527,6 +528,7 @@ __global__ __launch_bounds__(64) void trace_backward_kernel(const TraceJob *__re
         K.ry = (T)(dref * J.iw[1][c1]);
         K.rz = (T)(dref * J.iw[2][c2]);
     };
+    const int64_t nn = (int64_t)K.nx * K.ny * K.nz;
     unsigned long long n_half = 0, n_steps = 0, n_bad = 0, n_drop = 0;
     T cb[3][8], cj[3][8], gB[3][8], gJ[3][8];
     for (int c = 0; c < 3; c++)
@@ -649,7 +651,7 @@ __global__ __launch_bounds__(64) void trace_backward_kernel(const TraceJob *__re
                 for (int r = nrec - 1; r >= 0; r--) {
                     const StepRec sr = buf[r];
                     if (sr.c0 != cc0 || sr.c1 != cc1 || sr.c2 != cc2) {
-                        if (cc0 >= 0) flush_cell<T, TW>(bp.gnode, K.nx, K.ny, cc0, cc1, cc2, gB, gJ);
+                        if (cc0 >= 0) flush_cell<T, TW>(bp.gnode, nn, K.nx, K.ny, cc0, cc1, cc2, gB, gJ);
                         cc0 = sr.c0, cc1 = sr.c1, cc2 = sr.c2;
                         load_cell<T, S, TW>(J.nodes, K.nx, K.ny, cc0, cc1, cc2, cb, cj);
                         cell_scales(cc0, cc1, cc2);
@@ -658,7 +660,7 @@ __global__ __launch_bounds__(64) void trace_backward_kernel(const TraceJob *__re
                     step_adjoint<T, TW, SCH>(cb, cj, sr, K, sgn, endb, lam, ltw, gB, gJ);
                     n_steps++;
                 }
-                if (cc0 >= 0) flush_cell<T, TW>(bp.gnode, K.nx, K.ny, cc0, cc1, cc2, gB, gJ);
+                if (cc0 >= 0) flush_cell<T, TW>(bp.gnode, nn, K.nx, K.ny, cc0, cc1, cc2, gB, gJ);
                 if (ck == 0 && rj == 1 && bp.lam_seed) {
                     // a rotated-S0 line's adjoint at its seed, which depends on B0 (its
                     // offset along U or V): local units -> physical
@@ -719,9 +721,9 @@ __device__ __forceinline__ double dcoef_s(int m, int n, int N, const double *x)
 }
 
 // (D_axis)^T g at node (i, j, k): sum over the nodes m whose difference uses it; g is one
-// of the six values of a node
+// of the six values of a node, gs doubles from one node to the next
 // (x: the axis's node coordinates on a stretched axis, else NULL)
-__device__ double dT(const double *g, int axis, int i, int j, int k, int nx, int ny, int nz,
+__device__ double dT(const double *g, int64_t gs, int axis, int i, int j, int k, int nx, int ny, int nz,
                      double ih, const double *x)
 {
     const int N = axis == 0 ? nx : (axis == 1 ? ny : nz);
@@ -733,28 +735,28 @@ __device__ double dT(const double *g, int axis, int i, int j, int k, int nx, int
     for (int m = lo; m <= hi; m++) {
         if (m < 0 || m >= N) continue;
         const double c = x ? dcoef_s(m, n, N, x) : dcoef(m, n, N, ih);
-        if (c != 0.0) acc += c * g[6 * (q + (int64_t)(m - n) * stride)];
+        if (c != 0.0) acc += c * g[gs * (q + (int64_t)(m - n) * stride)];
     }
     return acc;
 }
 
 __global__ void grad_planes_kernel(int nx, int ny, int nz, double ihx, double ihy, double ihz,
                                    const double *cx, const double *cy, const double *cz,
-                                   const double *__restrict__ gnode, int want_tw, double *gx,
-                                   double *gy, double *gz)
+                                   const double *__restrict__ gnode, int64_t gs, int64_t gp,
+                                   int want_tw, double *gx, double *gy, double *gz)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int j = blockIdx.y, k = blockIdx.z;
     if (i >= nx) return;
     const int64_t q = ((int64_t)k * ny + j) * nx + i;
-    const double *gq = gnode + (want_tw ? 6 : 3) * q;
-    double bx = gq[0], by = gq[1], bz = gq[2];
+    const double *gq = gnode + gs * q;
+    double bx = gq[0], by = gq[gp], bz = gq[2 * gp];
     if (want_tw) {
         // J = (dBz/dy - dBy/dz, dBx/dz - dBz/dx, dBy/dx - dBx/dy)
-        const double *gjx = gnode + 3, *gjy = gnode + 4, *gjz = gnode + 5;
-        bx += dT(gjy, 2, i, j, k, nx, ny, nz, ihz, cz) - dT(gjz, 1, i, j, k, nx, ny, nz, ihy, cy);
-        by += dT(gjz, 0, i, j, k, nx, ny, nz, ihx, cx) - dT(gjx, 2, i, j, k, nx, ny, nz, ihz, cz);
-        bz += dT(gjx, 1, i, j, k, nx, ny, nz, ihy, cy) - dT(gjy, 0, i, j, k, nx, ny, nz, ihx, cx);
+        const double *gjx = gnode + 3 * gp, *gjy = gnode + 4 * gp, *gjz = gnode + 5 * gp;
+        bx += dT(gjy, gs, 2, i, j, k, nx, ny, nz, ihz, cz) - dT(gjz, gs, 1, i, j, k, nx, ny, nz, ihy, cy);
+        by += dT(gjz, gs, 0, i, j, k, nx, ny, nz, ihx, cx) - dT(gjx, gs, 2, i, j, k, nx, ny, nz, ihz, cz);
+        bz += dT(gjx, gs, 1, i, j, k, nx, ny, nz, ihy, cy) - dT(gjy, gs, 0, i, j, k, nx, ny, nz, ihx, cx);
     }
     gx[q] += bx;
     gy[q] += by;
@@ -836,7 +838,7 @@ __global__ void rot_seed_kernel(MapJob m, const RotEntry *__restrict__ rot,
         for (int c = 0; c < 3; c++) {
             const double gB = (gb[c] - b[c] * bb) / bm;
             if (gB == 0.0) continue;
-            for (int q = 0; q < 8; q++) atomicAdd(gnode + t.node[q] * m.gstride + c, gB * t.w[q]);
+            for (int q = 0; q < 8; q++) atomicAdd(gnode + t.node[q] * m.gstride + c * m.gplane, gB * t.w[q]);
         }
     }
 }
@@ -904,7 +906,7 @@ hipError_t launch_trace_backward(int store, int want_tw, const TraceJob *job_dev
     // FP64 adaptive steps with four lanes to a half line. FP32 ones stay with one lane: the
     // gradient sums of a cell are FP32 there, and summing them in another order moves the
     // gradient by 2e-6 of its size.
-    if (bp.scheme == SCH_RKF45 && store == FQ_DT_F64) return launch_trace_backward_quad(want_tw, job_dev, bp, s);
+    if (reverse_in_quads(store == FQ_DT_F64, bp.scheme)) return launch_trace_backward_quad(want_tw, job_dev, bp, s);
     if (bp.scheme == SCH_RKF45) launch_bwd_s<SCH_RKF45>(store, want_tw, job_dev, bp, s);
     else if (bp.scheme == SCH_RK4) launch_bwd_s<SCH_RK4>(store, want_tw, job_dev, bp, s);
     else if (bp.scheme == SCH_RK4_38) launch_bwd_s<SCH_RK4_38>(store, want_tw, job_dev, bp, s);
@@ -912,14 +914,17 @@ hipError_t launch_trace_backward(int store, int want_tw, const TraceJob *job_dev
     return hipGetLastError();
 }
 
-hipError_t launch_grad_planes(const fq_field &f, const double *gnode, int want_tw,
+hipError_t launch_grad_planes(const fq_field &f, const double *gnode, int form,
                               double *const gb[3], hipStream_t s)
 {
+    const int want_tw = form & kGradTwist;
+    const bool planes = (form & kGradPlanes) != 0;
+    const int64_t gs = planes ? 1 : (want_tw ? 6 : 3), gp = planes ? f.n[0] * f.n[1] * f.n[2] : 1;
     const unsigned bxs = (unsigned)((f.n[0] + 255) / 256);
     hipLaunchKernelGGL(grad_planes_kernel, dim3(bxs, (unsigned)f.n[1], (unsigned)f.n[2]), dim3(256),
                        0, s, (int)f.n[0], (int)f.n[1], (int)f.n[2], 1.0 / f.spacing[0],
                        1.0 / f.spacing[1], 1.0 / f.spacing[2], f.coord[0], f.coord[1], f.coord[2],
-                       gnode, want_tw, gb[0], gb[1], gb[2]);
+                       gnode, gs, gp, want_tw, gb[0], gb[1], gb[2]);
     return hipGetLastError();
 }
 

@@ -430,6 +430,8 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
             FQ_TRY(launch_prep(*s.f, FQ_PREC_F64, P.want_tw, ws + w.nodes64, (float *)(ws + w.bmax),
                                stream));
     }
+    // how the adjoint's node gradients lie
+    const bool gplanes = !reverse_in_quads(P.precision == FQ_PREC_F64, P.scheme);
     // rotated-S0 classification (each map with an interior S0)
     std::vector<MapJob> maps(ns);
     for (int i = 0; i < ns; i++) {
@@ -439,7 +441,8 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
         memset(&m, 0, sizeof m);
         set_map_geometry(s, m);
         m.edge_eps = P.edge_eps;
-        m.gstride = P.want_tw ? 6 : 3;
+        m.gstride = gplanes ? 1 : (P.want_tw ? 6 : 3);
+        m.gplane = gplanes ? nodes_of(s.f) : 1;
         m.rec = recs_at(ws, w.end, w.tw, w.len, w.face, w.st);
         if (m2) m.rec.uv = (double *)(ws + w.uv);
         m.nlines = w.nlines;
@@ -769,7 +772,9 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
             FQ_TRY(launch_rot_seed(maps[0], (const RotEntry *)(ws + W[0].rot),
                                    (const uint32_t *)(ws + W[0].rot_count), W[0].nlines, lseed, gnode,
                                    stream));
-        FQ_TRY(launch_grad_planes(*specs[0].f, gnode, P.want_tw, bwd->gb, stream));
+        FQ_TRY(launch_grad_planes(*specs[0].f, gnode,
+                                  (P.want_tw ? kGradTwist : 0) | (gplanes ? kGradPlanes : 0), bwd->gb,
+                                  stream));
         return FQ_OK;
     }
     for (int i = 0; i < ns; i++) {

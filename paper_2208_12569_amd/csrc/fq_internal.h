@@ -163,9 +163,7 @@ struct BwdParams {
     int64_t nhalves;               // 2 * nlines
     const double *lam_end;         // per half: dL/d(end point), 3 doubles
     const double *lam_tw;          // per half: dL/d(Tw of the half)
-    // per node dL/d(Bx, By, Bz) and, with twist, dL/d(Jx, Jy, Jz) side by side: the lanes of
-    // a half line add to one or two cache lines instead of six
-    double *gnode;
+    double *gnode;                 // per node dL/d(Bx, By, Bz) and, with twist, dL/d(Jx, Jy, Jz)
     StepRec *buf;                  // nslots * seg replay records
     int64_t nslots;                // half lines in the reverse kernel at once
     unsigned long long *counter;   // queue
@@ -246,7 +244,8 @@ struct MapJob {
     int32_t n[3];
     double origin[3], spacing[3];
     const double *coord[3];  // node coordinates of stretched axes (NULL = uniform axis)
-    int64_t gstride;             // adjoint: doubles per node in gnode (below)
+    int64_t gstride, gplane;     // adjoint: doubles in gnode from one node to the next and from
+                                 // one of a node's values to the next
     int64_t nu, nv, nlayers;     // points per layer = nu*nv
     double d0, d1;               // seed spacing along the two S0 axes
     double normal[3];            // S0 normal
@@ -280,7 +279,18 @@ hipError_t launch_trace_backward(int store, int want_tw, const TraceJob *job_dev
 // RKF45's in FP64, with four lanes to a half line (adjoint_quad.hip)
 hipError_t launch_trace_backward_quad(int want_tw, const TraceJob *job_dev, const BwdParams &bp,
                                       hipStream_t s);
-hipError_t launch_grad_planes(const fq_field &f, const double *gnode, int want_tw,
+// Whether the reverse kernel takes four lanes to a half line. That also decides how the node
+// gradients lie. With four lanes the three values that a half line's lanes add to a node
+// lie side by side, in one cache line instead of three. With one lane to a half line each
+// of the six is a plane of its own: the lanes of a wave run along neighbouring lines and
+// add the same value of nearby nodes at once. (Side by side there: map, loss and gradient
+// in F32X of 288 x 288 points inside a 96x96x72 grid 15.7 -> 20.6 ms, of a 40x40x30 voxel
+// map 14.0 -> 17.0 ms; RK4 in FP64 at 128 x 128 6.8 -> 7.1 ms. Planes for the four-lane
+// kernel: a 256 x 256 plane of a 128x128x96 grid 6.2 -> 7.6 ms.)
+inline bool reverse_in_quads(bool f64, int scheme) { return f64 && scheme == FQ_SCHEME_RKF45; }
+// form: kGradTwist with twist, kGradPlanes if each value has a plane of its own
+constexpr int kGradTwist = 1, kGradPlanes = 2;
+hipError_t launch_grad_planes(const fq_field &f, const double *gnode, int form,
                               double *const gb[3], hipStream_t s);
 constexpr int64_t kBwdSlots = 32768;  // half lines in the reverse kernel at once
 

@@ -1,0 +1,48 @@
+"""Which form of a kernel a call takes: the rules of the host layer, read off the
+arguments of its launches (no GPU needed). Each rule's reason and measured figures stand
+beside it in the sources."""
+
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2208_12569_amd", "csrc")
+F32X, F64 = 0, 1
+I, II = 0, 1
+RKF45, RK4, RK4_38 = 0, 1, 2
+GPP = ["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__=1", "-I/opt/rocm/include", "-I",
+       os.path.join(ROOT, "include"), "-I", CSRC]
+
+
+@pytest.fixture(scope="module")
+def route(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("routes") / "route_driver")
+    subprocess.check_call([*GPP, os.path.join(CSRC, "api.cpp"),
+                           os.path.join(ROOT, "tests", "sanitize", "route_driver.cpp"), "-o", exe])
+
+    def call(kind, n, seeds, precision=F32X, method=I, scheme=RKF45, in_flight=0, waves=0, height=0.0, jobs=1):
+        seeds = tuple(seeds) + (1,) * (3 - len(seeds))
+        args = [kind, *n, *seeds, precision, method, scheme, in_flight, waves, height, jobs]
+        r = subprocess.run([exe, *(str(a) for a in args)], capture_output=True, text=True)
+        assert r.returncode == 0, (args, r.stdout, r.stderr)
+        return {k: int(v) for k, v in (line.split() for line in r.stdout.splitlines())}
+
+    return call
+
+
+@pytest.mark.parametrize("kind,height", [("fit", 0.0), ("fit", 0.13), ("fit3", 0.0)])
+@pytest.mark.parametrize("precision,scheme", [(F32X, RKF45), (F32X, RK4), (F64, RKF45), (F64, RK4), (F64, RK4_38)])
+def test_gradient_layout_follows_the_reverse_kernel(route, kind, height, precision, scheme):
+    """Node gradients lie side by side only for the reverse kernel whose half lines have a
+    lane per component (FP64, RKF45); with one lane to a half line each component has a
+    plane of its own, where neighbouring lines' additions share cache lines."""
+    n = (40, 36, 30)
+    if scheme != RKF45 and (kind == "fit3" or height):
+        pytest.skip("fixed steps differentiate planes on a face only")
+    r = route(kind, n, (12, 11, 5), precision=precision, scheme=scheme, height=height)
+    if precision == F64 and scheme == RKF45:
+        assert (r["node_step"], r["value_step"], r["grad_form"]) == (6, 1, 1)
+    else:
+        assert (r["node_step"], r["value_step"], r["grad_form"]) == (1, 40 * 36 * 30, 3)
