@@ -467,20 +467,30 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
     for (int i = 0; i < ns; i++)
         live_lines += W[i].nlines * (specs[i].kind == SPEC_PLANE && plane_on_face(specs[i].pl, *specs[i].f) ? 1 : 2);
     const bool ordered = live_lines > kLanes || P.waves_per_cu > 0;
-    // Four lanes to a half line (trace_quad.hip) up to here. The longer the lines, the
-    // later the chip is full enough for one lane to a line to catch up; past 131072 the
-    // eight waves a SIMD that the quads then need no longer fit beside each other. The
-    // trace with one lane over that with four, by live half lines (plane, FP32 / FP64,
-    // interior cut and voxel map of a few random fields):
+    // Four lanes to a half line (trace_quad.hip) up to here: where the two kernels cross in
+    // time, later the longer the lines. The trace with one lane over that with four, by live
+    // half lines (plane, FP32 / FP64, interior cut and voxel map of a few random fields):
     //     64^3           50176 1.08 / 1.23 / 1.10 / 1.10,  92416 1.01 / 1.10 / 1.08 / 0.98,
     //                   129600 0.92 / 0.98 / 1.01 / 0.89
     //     256 x 256 x 128  the same three: 1.16 / 1.22 / 1.15 / 1.16,
     //                   1.15 / 1.33 / 1.15 / 1.05, 1.05 / 1.21 / 1.15 / 1.01
     // and at 262144 on stretched and Method II planes of 256-node grids 0.89 / 0.92.
+    // (The grid of either kernel is full well before that: two to four waves per SIMD, so
+    // 16 to 64 thousand half lines in quads, the others wait in the queue.)
+    // Calls with other maps in flight share the chip with them, and the kernels cross at a
+    // part of that count. Eight maps of a 4:4:3 grid, four in flight, all with one lane over
+    // all with four, by half lines a map:
+    //     F32X   64 nodes long  16384 1.02, 20736 0.99, 25600 0.94, 36864 0.94, 50176 0.83
+    //           128 nodes long  16384 1.05, 20736 1.00, 25600 0.98, 36864 0.96, 50176 0.90
+    //           256 nodes long  16384 1.08, 25600 1.02, 36864 1.01, 50176 0.94, 65536 0.88
+    //     F64    64 nodes long  16384 1.05, 25600 1.04, 30976 1.03, 36864 0.94, 50176 0.86
+    //           128 nodes long  16384 1.07, 25600 1.07, 36864 1.03, 43264 0.93, 50176 0.90
+    //           256 nodes long  16384 1.09, 25600 1.11, 36864 1.01, 43264 1.01, 50176 0.95
     int64_t longest = 0;
     for (int i = 0; i < ns; i++)
         for (int a = 0; a < 3; a++) longest = std::max<int64_t>(longest, specs[i].f->n[a]);
-    const int64_t few_lines = std::min<int64_t>(131072, 65536 + 256 * longest);
+    int64_t few_lines = std::min<int64_t>(131072, 65536 + 256 * longest);
+    if (P.in_flight) few_lines = P.precision == FQ_PREC_F64 ? few_lines * 2 / 5 : few_lines / 4;
     // job table
     std::vector<TraceJob> jobs(njobs);
     int64_t items = 0;

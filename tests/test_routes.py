@@ -46,3 +46,19 @@ def test_gradient_layout_follows_the_reverse_kernel(route, kind, height, precisi
         assert (r["node_step"], r["value_step"], r["grad_form"]) == (6, 1, 1)
     else:
         assert (r["node_step"], r["value_step"], r["grad_form"]) == (1, 40 * 36 * 30, 3)
+
+
+@pytest.mark.parametrize("precision", [F32X, F64])
+@pytest.mark.parametrize("edge", [64, 128, 256, 400])
+def test_four_lanes_to_a_line_up_to_a_share_of_the_chip(route, edge, precision):
+    """Up to 65536 half lines and 256 for each node of the longest axis, at most 131072; of
+    that a quarter (F32X) or two fifths (F64) where other maps are in flight."""
+    n = (edge, edge, edge * 3 // 4)
+    most = min(131072, 65536 + 256 * edge)
+    for in_flight, limit in ((0, most), (1, most // 4 if precision == F32X else most * 2 // 5)):
+        for seeds in (1, 64, 1000, limit - 1, limit, limit + 1, 3 * limit):
+            r = route("plane", n, (seeds, 1), precision=precision, in_flight=in_flight)
+            assert r["few"] == (seeds <= limit), (seeds, limit, in_flight)
+            # an interior plane traces both halves of each line
+            r = route("plane", n, (seeds, 1), precision=precision, in_flight=in_flight, height=0.2)
+            assert r["few"] == (2 * seeds <= limit), (seeds, limit, in_flight)
