@@ -27,8 +27,7 @@ struct Carve {
     }
 };
 
-// lanes of one wave per SIMD on every CU
-constexpr int64_t kLanes = 256 * 4 * 64;
+constexpr int64_t kSimds = 256 * 4;
 
 enum SpecKind { SPEC_LIST, SPEC_PLANE, SPEC_VOXELS, SPEC_CYL };
 
@@ -460,13 +459,28 @@ int run(const std::vector<Spec> &specs, const fq_params &P, char *ws, size_t ws_
                                        (uint32_t *)(ws + w.rot_count), w.nlines, stream));
         }
     }
-    // The tiles are put in order only where some lines have to wait for others to end:
-    // a call whose lines all start at once (at most 64 per SIMD, which every tracer grid
-    // holds) gains nothing from it.
+    // The tiles are put in order only where that gains more than its own launches take (40
+    // to 60 us a plane, the longest coarse line): waves of like lines end together, and the
+    // long ones start first. That is from about one wave of quads per SIMD on for a plane by
+    // itself, from two on in F32X, where half of the call is the FP64 pass, whose list keeps
+    // its own order. Voxel maps, whose order is by footpoints, and batches, which pay one
+    // order per plane, take it from one wave of 64 lines per SIMD on. The call without an order over that with one, by half lines, on 64x64x48 and 192x192x144:
+    //     F64            12100 0.98 / 1.00, 16384 1.03 / 1.04, 19600 1.07 / 1.06, 28900 1.17 / 1.15,
+    //                    57600 1.21 / 1.25
+    //     F64, cut       12800 0.96 / 0.94, 20000 1.02 / 0.99, 32258 1.11 / 1.07, 57800 1.27 / 1.25
+    //     F64, Method II 12100 1.00 / 0.99, 16384 1.05 / 1.08, 28900 1.12 / 1.21, 57600 1.25 / 1.27
+    //     F32X           16384 0.98 / 0.97, 25600 0.97 / 0.99, 28900 1.02 / 1.02, 36100 1.02 / 1.04,
+    //                    57600 1.08 / 1.12
+    //     F32X, cut      20000 0.97 / 0.97, 32258 0.99 / 0.98, 45000 1.02 / 1.03, 64800 1.06 / 1.06
+    //     F32X, Method II 12100 1.00 / 1.03, 16384 1.04 / 1.01, 28900 1.10 / 1.10, 57600 1.14 / 1.15
+    //     voxels         16000 0.85 to 0.94, 31250 0.89 to 0.93, 65536 0.93 to 0.95
     int64_t live_lines = 0;
     for (int i = 0; i < ns; i++)
         live_lines += W[i].nlines * (specs[i].kind == SPEC_PLANE && plane_on_face(specs[i].pl, *specs[i].f) ? 1 : 2);
-    const bool ordered = live_lines > kLanes || P.waves_per_cu > 0;
+    const int64_t unordered = ns > 1 || specs[0].kind != SPEC_PLANE ? 64 * kSimds
+                              : P.precision == FQ_PREC_F64 || m2    ? 15 * kSimds
+                                                                    : 32 * kSimds;
+    const bool ordered = live_lines > unordered || P.waves_per_cu > 0;
     // Four lanes to a half line (trace_quad.hip) up to here: where the two kernels cross in
     // time, later the longer the lines. The trace with one lane over that with four, by live
     // half lines (plane, FP32 / FP64, interior cut and voxel map of a few random fields):

@@ -62,3 +62,25 @@ def test_four_lanes_to_a_line_up_to_a_share_of_the_chip(route, edge, precision):
             # an interior plane traces both halves of each line
             r = route("plane", n, (seeds, 1), precision=precision, in_flight=in_flight, height=0.2)
             assert r["few"] == (2 * seeds <= limit), (seeds, limit, in_flight)
+
+
+@pytest.mark.parametrize("precision,method,limit", [(F32X, I, 32768), (F32X, II, 15360), (F64, I, 15360), (F64, II, 15360)])
+def test_tiles_of_a_plane_are_ordered_from_a_wave_or_two_per_simd(route, precision, method, limit):
+    """A plane by itself: from about one wave of quads per SIMD on, two in F32X. A chosen
+    residency (waves_per_cu) always orders."""
+    n = (64, 64, 48)
+    for height in (0.0, 0.2):
+        lines = limit if height == 0.0 else limit // 2
+        for seeds, want in ((16, 0), (lines, 0), (lines + 1, 1), (65536, 1), (300000, 1)):
+            r = route("plane", n, (seeds, 1), precision=precision, method=method, height=height)
+            assert r["orders"] == want, (seeds, height)
+    assert route("plane", n, (16, 1), precision=precision, method=method, waves=4)["orders"] == 1
+
+
+@pytest.mark.parametrize("precision", [F32X, F64])
+def test_voxels_and_batches_are_ordered_above_a_wave_of_lines_per_simd(route, precision):
+    n = (64, 64, 48)
+    for edge, want in ((8, 0), (32, 0), (33, 1)):
+        assert route("voxels", n, (edge, edge, edge), precision=precision)["orders"] == want, edge
+    for jobs, seeds, want in ((16, 4096, 0), (16, 4097, 16), (2, 30000, 0), (2, 40000, 2)):
+        assert route("plane", n, (seeds, 1), precision=precision, jobs=jobs)["orders"] == want, (jobs, seeds)
