@@ -210,8 +210,16 @@ hipError_t launch_trace(int prec, int store, int twm, const TraceJob *jobs_dev,
 // The same with four lanes to a half line (trace_quad.hip), if the queue holds at most
 // `most` items (else the kernel ends at once).
 hipError_t launch_trace_quad(bool f64, bool s64, int twm, const TraceJob *jobs_dev, const TraceParams &tp,
-                             unsigned long long *counter, int64_t most, int ncu, int waves_per_cu,
-                             hipStream_t s);
+                             unsigned long long *counter, int64_t most, int ncu, int block,
+                             int waves_per_cu, hipStream_t s);
+// Blocks of a tracer kernel per CU: the most that fit, or as many as hold waves_per_cu waves.
+inline int tracer_blocks_per_cu(const void *fn, int block, int waves_per_cu)
+{
+    int fit = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, fn, block, 0) != hipSuccess || fit < 1) fit = 1;
+    const int64_t want = ((int64_t)waves_per_cu * 64 + block - 1) / block;
+    return waves_per_cu > 0 && want < fit ? (int)want : fit;
+}
 // Order n items longest first: key (n values, 0..255 = longest; overwritten with the
 // bucket), counts (256), order (n: the item indices in queue order) are workspace.
 hipError_t launch_bucket_order(int64_t n, int32_t *key, uint32_t *counts, int32_t *order,

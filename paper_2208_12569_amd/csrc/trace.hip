@@ -1091,7 +1091,8 @@ hipError_t launch_trace(int prec, int store, int twm, const TraceJob *jobs_dev,
     if (!tp.cyl && tp.scheme == SCH_RKF45) {
         if (!tp.list) {
             if (tp.few)
-                return launch_trace_quad(f64, s64, twm, jobs_dev, tp, counter, INT64_MAX, ncu, waves_per_cu, s);
+                return launch_trace_quad(f64, s64, twm, jobs_dev, tp, counter, INT64_MAX, ncu, block,
+                                         waves_per_cu, s);
         } else {
             // Re-trace lists, whose lengths are on the device: one of the two kernels finds
             // nothing to do. Up to kFewList halves four lanes to a line (65536: the list of a
@@ -1100,19 +1101,12 @@ hipError_t launch_trace(int prec, int store, int twm, const TraceJob *jobs_dev,
             // 178.0 ms for 175.0). The half lines still on their way at the end of the FP32
             // pass are few by nature.
             const hipError_t e = launch_trace_quad(f64, s64, twm, jobs_dev, tp, counter,
-                                                   tp.list_rev ? INT64_MAX : kFewList, ncu, waves_per_cu, s);
+                                                   tp.list_rev ? INT64_MAX : kFewList, ncu, block, waves_per_cu, s);
             if (e != hipSuccess || tp.list_rev) return e;
             p.least = kFewList;
         }
     }
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, block, 0) != hipSuccess) per_cu = 0;
-    if (per_cu <= 0) per_cu = 1;
-    if (waves_per_cu > 0) {
-        int want = (waves_per_cu * 64 + block - 1) / block;
-        if (want < per_cu) per_cu = want;
-        if (per_cu < 1) per_cu = 1;
-    }
+    const int per_cu = tracer_blocks_per_cu(fn, block, waves_per_cu);
     void *args[3] = {&jobs_dev, &p, &counter};
     return hipLaunchKernel(fn, dim3((unsigned)(per_cu * ncu)), dim3((unsigned)block), args, 0, s);
 }

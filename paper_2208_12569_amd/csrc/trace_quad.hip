@@ -13,7 +13,6 @@
 // batch 32.7 -> 27.1 ms; the map, loss and gradient of a 256 x 256 plane, whose forward
 // pass this is as well, 6.26 -> 6.12 ms.
 #include "fq_internal.h"
-#include <algorithm>
 #include "trace_quad.h"
 
 namespace fq {
@@ -331,17 +330,15 @@ template <typename T, typename S> const void *pick(int twm, const TraceParams &t
 }  // namespace
 
 hipError_t launch_trace_quad(bool f64, bool s64, int twm, const TraceJob *jobs_dev, const TraceParams &tp,
-                             unsigned long long *counter, int64_t most, int ncu, int waves_per_cu,
-                             hipStream_t s)
+                             unsigned long long *counter, int64_t most, int ncu, int block,
+                             int waves_per_cu, hipStream_t s)
 {
     const void *fn = !f64 ? pick<float, float>(twm, tp)
                      : s64 ? pick<double, double>(twm, tp) : pick<double, float>(twm, tp);
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 256, 0) != hipSuccess || per_cu <= 0) per_cu = 1;
-    if (waves_per_cu > 0) per_cu = std::max(1, std::min(per_cu, waves_per_cu / 4));
+    const int per_cu = tracer_blocks_per_cu(fn, block, waves_per_cu);
     TraceParams p = tp;
     void *args[4] = {&jobs_dev, &p, &counter, &most};
-    return hipLaunchKernel(fn, dim3((unsigned)(per_cu * ncu)), dim3(256), args, 0, s);
+    return hipLaunchKernel(fn, dim3((unsigned)(per_cu * ncu)), dim3((unsigned)block), args, 0, s);
 }
 
 }  // namespace fq

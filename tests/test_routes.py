@@ -1,5 +1,5 @@
-"""Which form of a kernel a call takes: the rules of the host layer, read off the
-arguments of its launches (no GPU needed). Each rule's reason and measured figures stand
+"""Which form of a kernel a call takes, and with what launch shape: the rules of the host
+code, read off the arguments of its launches (no GPU needed). Each rule's reason and measured figures stand
 beside it in the sources."""
 
 import os
@@ -29,6 +29,36 @@ def route(tmp_path_factory):
         assert r.returncode == 0, (args, r.stdout, r.stderr)
         return {k: int(v) for k, v in (line.split() for line in r.stdout.splitlines())}
 
+    return call
+
+
+@pytest.fixture(scope="module")
+def launches(tmp_path_factory):
+    """(status, [(blocks, threads, kernel)]) of the launchers' host code."""
+    from paper_2208_12569_amd import build
+
+    d = tmp_path_factory.mktemp("launches")
+    objs = []
+    for src in ("trace", "trace_quad", "prep"):
+        objs.append(str(d / f"{src}.o"))
+        subprocess.check_call([build.HIPCC, "--offload-arch=gfx950", "--offload-host-only", "-O0", "-std=c++17", "-w",
+                               "-I", build.INCLUDE, "-I", CSRC, "-c", os.path.join(CSRC, f"{src}.hip"), "-o", objs[-1]])
+    exe = str(d / "launch_driver")
+    # (the device code these objects would carry is left out)
+    subprocess.check_call([*GPP, "-no-pie", os.path.join(ROOT, "tests", "sanitize", "launch_driver.cpp"), *objs,
+                           "-Wl,--unresolved-symbols=ignore-all", "-o", exe])
+
+    def call(*args):
+        r = subprocess.run([exe, *(str(int(a) if isinstance(a, bool) else a) for a in args)], capture_output=True, text=True)
+        assert r.returncode == 0, (args, r.stdout, r.stderr)
+        *rows, status = r.stdout.splitlines()
+        return int(status.split()[1]), [(int(g), int(b), k) for g, b, k in (x.split(" ", 2) for x in rows)]
+
+    def trace(precision=F64, store=1, twm=1, list_=0, rev=0, few=0, cyl=0, scheme=RKF45, method=I, jobs=1, tape=0,
+              block=0, waves=0):
+        return call("trace", precision, store, twm, list_, rev, few, cyl, scheme, method, jobs, tape, block, waves)
+
+    call.trace = trace
     return call
 
 
@@ -84,3 +114,19 @@ def test_voxels_and_batches_are_ordered_above_a_wave_of_lines_per_simd(route, pr
         assert route("voxels", n, (edge, edge, edge), precision=precision)["orders"] == want, edge
     for jobs, seeds, want in ((16, 4096, 0), (16, 4097, 16), (2, 30000, 0), (2, 40000, 2)):
         assert route("plane", n, (seeds, 1), precision=precision, jobs=jobs)["orders"] == want, (jobs, seeds)
+
+
+@pytest.mark.parametrize("block", [0, 64, 128, 192, 256])
+@pytest.mark.parametrize("waves", [0, 1, 4, 6, 12, 64])
+def test_every_tracer_launch_takes_the_callers_shape(launches, block, waves):
+    """block threads (256 by default) and as many blocks a CU as hold waves_per_cu waves, in
+    the one-lane and the four-lane kernel, of maps and of re-trace lists."""
+    threads = block or 256
+    per_cu = 2048 // threads
+    if waves:
+        per_cu = min(per_cu, -(-waves * 64 // threads))
+    for kw in (dict(few=0), dict(few=1), dict(few=1, method=II), dict(list_=1, twm=2), dict(list_=1, rev=1)):
+        status, rows = launches.trace(block=block, waves=waves, **kw)
+        assert status == 0 and rows
+        for grid, thr, kernel in rows:
+            assert (grid, thr) == (256 * per_cu, threads), (kw, kernel)
