@@ -78,6 +78,7 @@ template <> struct V4<double> { using t = double4; };
 // reaches 5.1), 384^3 1.70 -> 0.60 ms, 256x256x128 0.19 -> 0.10 ms, 64^3 (where most lanes
 // were past the row's end) 35 -> 19 us; FP32 planes to FP64 records of 384^3 2.39 -> 1.01 ms.
 constexpr int kRows = 4;
+constexpr int64_t kMostBlocks = 1 << 23;
 
 template <typename S, typename T, bool TW>
 __global__ __launch_bounds__(256) void prep_kernel(const S *__restrict__ bx,
@@ -280,6 +281,9 @@ hipError_t run_prep(const fq_field &f, int want_tw, void *A, float *bmax2, hipSt
     // than 32 rows (the row before the first is read twice)
     int64_t depth = tx * tz * f.n[1] / 4096;
     depth = depth < 1 ? 1 : (depth > 32 ? 32 : depth);
+    // (a launch has less than 2^32 threads, which thin grids of 4e9 nodes would pass)
+    const int64_t pieces = kMostBlocks / (tx * tz);
+    if (pieces * depth < f.n[1]) depth = pieces > 1 ? (f.n[1] + pieces - 1) / pieces : f.n[1];
     int64_t blocks = tx * tz * ((f.n[1] + depth - 1) / depth);
     blocks = (blocks + 7) / 8 * 8;
     const auto fn = want_tw ? prep_kernel<S, T, true> : prep_kernel<S, T, false>;

@@ -130,3 +130,16 @@ def test_every_tracer_launch_takes_the_callers_shape(launches, block, waves):
         assert status == 0 and rows
         for grid, thr, kernel in rows:
             assert (grid, thr) == (256 * per_cu, threads), (kw, kernel)
+
+
+@pytest.mark.parametrize("n", [(2, 65535, 65535), (2, 65535, 32768), (3, 65535, 32000), (65, 8000, 12500), (65535, 2, 49000),
+                               (65535, 49000, 2), (2, 2, 65535), (2048, 2048, 1500), (64, 64, 64), (5, 9, 6)])
+@pytest.mark.parametrize("tw", [0, 1])
+def test_prep_launch_fits_every_grid_that_memory_holds(launches, n, tw):
+    """Fewer than 2^32 threads in a launch, for grids up to what 288 GB hold (28 bytes a
+    node with FP32 records, 44 with twist)."""
+    assert n[0] * n[1] * n[2] * 28 < 288e9
+    status, rows = launches("prep", *n, 0, F32X, tw)
+    assert status == 0 and len(rows) == 1
+    grid, threads, _ = rows[0]
+    assert threads == 256 and 0 < grid * threads < 1 << 32
