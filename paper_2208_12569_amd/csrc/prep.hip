@@ -80,6 +80,16 @@ template <> struct V4<double> { using t = double4; };
 constexpr int kRows = 4;
 constexpr int64_t kMostBlocks = 1 << 23;
 
+// LDS that a wave's lanes exchange among themselves: what was written before is there for
+// the other lanes after, and what was read before is read (no instruction, but the
+// compiler moves no access across).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 template <typename S, typename T, bool TW>
 __global__ __launch_bounds__(256) void prep_kernel(const S *__restrict__ bx,
                                                    const S *__restrict__ by,
@@ -176,17 +186,17 @@ __global__ __launch_bounds__(256) void prep_kernel(const S *__restrict__ bx,
                     c.y = (T)(dxy - dyx);
                     c.z = (T)0;
                     c.w = (T)0;
-                    // the wave's 64 records in memory order (a wave's own rows: no barrier)
+                    // the wave's 64 records in memory order (a wave's own rows: no block barrier)
                     V *own = (V *)&out[w][kPieces * lane];
                     own[0] = a;
                     own[1] = c;
-                    __builtin_amdgcn_wave_barrier();
+                    wave_sync();
                     Piece *row = (Piece *)(A + 2 * ((int64_t)k * nxy + (int64_t)j * nx + ib * 64));
                     const int live = kPieces * min(64, nx - ib * 64);
 #pragma unroll
                     for (int u = 0; u < kPieces; u++)
                         if (lane + 64 * u < live) row[lane + 64 * u] = out[w][lane + 64 * u];
-                    __builtin_amdgcn_wave_barrier();
+                    wave_sync();
                 } else if (in) {
                     A[p] = a;
                 }
