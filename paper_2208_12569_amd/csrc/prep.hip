@@ -90,7 +90,30 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <typename S, typename T, bool TW>
+// The block's maximum to *bmax2, one atomic per block of 256 (non-negative floats order
+// like ints).
+__device__ __forceinline__ void block_max(float local, float *__restrict__ bmax2)
+{
+    for (int off = 32; off > 0; off >>= 1) {
+        const float o = __shfl_xor(local, off);
+        local = o > local ? o : local;
+    }
+    __shared__ float wmax[4];
+    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = local;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float m = 0.0f;
+        for (int v = 0; v < 4; v++) m = wmax[v] > m ? wmax[v] : m;
+        if (m > 0.0f) {
+            if (m > FLT_MAX) m = FLT_MAX;
+            // (most blocks see a larger maximum there already: thousands of atomics on one
+            // word take longer than the pass)
+            if (m > *(volatile float *)bmax2) atomicMax((int *)bmax2, __float_as_int(m));
+        }
+    }
+}
+
+template <typename S, typename T>
 __global__ __launch_bounds__(256) void prep_kernel(const S *__restrict__ bx,
                                                    const S *__restrict__ by,
                                                    const S *__restrict__ bz, int nx, int ny,
@@ -107,7 +130,7 @@ __global__ __launch_bounds__(256) void prep_kernel(const S *__restrict__ bx,
     // 16-byte pieces of the four waves' 64 records
     typedef float Piece __attribute__((ext_vector_type(4)));
     constexpr int kPieces = 2 * sizeof(V) / sizeof(Piece);
-    __shared__ Piece out[TW ? 4 : 1][TW ? 64 * kPieces : 1];
+    __shared__ Piece out[4][64 * kPieces];
     const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
     const int64_t nxy = (int64_t)nx * ny;
     // patch of this block: gridDim.x / 8 consecutive ones per XCD (the grid is rounded up)
@@ -130,7 +153,7 @@ __global__ __launch_bounds__(256) void prep_kernel(const S *__restrict__ bx,
         const int64_t zs = zin ? nxy : 0, xs = xin ? 1 : 0;
         // Bx and Bz one row below and at the node
         S xm = S(0), zm = S(0), x0 = bx[q], z0 = bz[q];
-        if (TW && j0 > 0) xm = bx[q - nx], zm = bz[q - nx];
+        if (j0 > 0) xm = bx[q - nx], zm = bz[q - nx];
         for (int jr = (int)j0; jr < j1; jr += kRows) {
             // all of these rows' values first: the pass waits on memory, so what counts is
             // how much a wave has on its way at once
@@ -144,12 +167,10 @@ __global__ __launch_bounds__(256) void prep_kernel(const S *__restrict__ bx,
                 X[v + 2] = bx[pn];
                 Z[v + 2] = bz[pn];
                 Y[v] = by[p];
-                if (TW) {
-                    Xl[v] = bx[p - zs], Xh[v] = bx[p + zs];
-                    Yl[v] = by[p - zs], Yh[v] = by[p + zs];
-                    Zw[v] = bz[p - xs], Ze[v] = bz[p + xs];
-                    Yw[v] = by[p - xs], Ye[v] = by[p + xs];
-                }
+                Xl[v] = bx[p - zs], Xh[v] = bx[p + zs];
+                Yl[v] = by[p - zs], Yh[v] = by[p + zs];
+                Zw[v] = bz[p - xs], Ze[v] = bz[p + xs];
+                Yw[v] = by[p - xs], Ye[v] = by[p + xs];
             }
 #pragma unroll
             for (int v = 0; v < kRows; v++) {
@@ -161,45 +182,40 @@ __global__ __launch_bounds__(256) void prep_kernel(const S *__restrict__ bx,
                 a.x = (T)dx0;
                 a.y = (T)dy0;
                 a.z = (T)dz0;
-                a.w = (T)0;
-                if (TW) {
-                    double dyx = ((double)X[v + 2] - (double)X[v]) * (0.5 * ihy);
-                    double dyz = ((double)Z[v + 2] - (double)Z[v]) * (0.5 * ihy);
-                    double dzx = ((double)Xh[v] - (double)Xl[v]) * (0.5 * ihz);
-                    double dzy = ((double)Yh[v] - (double)Yl[v]) * (0.5 * ihz);
-                    double dxz = ((double)Ze[v] - (double)Zw[v]) * (0.5 * ihx);
-                    double dxy = ((double)Ye[v] - (double)Yw[v]) * (0.5 * ihx);
-                    if (cy || j == 0 || j == ny - 1) {
-                        dyx = dax(bx, p, j, ny, nx, ihy, cy);
-                        dyz = dax(bz, p, j, ny, nx, ihy, cy);
-                    }
-                    if (!zin) {
-                        dzx = dax(bx, p, k, nz, nxy, ihz, cz);
-                        dzy = dax(by, p, k, nz, nxy, ihz, cz);
-                    }
-                    if (!xin) {
-                        dxz = dax(bz, p, iq, nx, 1, ihx, cx);
-                        dxy = dax(by, p, iq, nx, 1, ihx, cx);
-                    }
-                    a.w = (T)(dyz - dzy);
-                    c.x = (T)(dzx - dxz);
-                    c.y = (T)(dxy - dyx);
-                    c.z = (T)0;
-                    c.w = (T)0;
-                    // the wave's 64 records in memory order (a wave's own rows: no block barrier)
-                    V *own = (V *)&out[w][kPieces * lane];
-                    own[0] = a;
-                    own[1] = c;
-                    wave_sync();
-                    Piece *row = (Piece *)(A + 2 * ((int64_t)k * nxy + (int64_t)j * nx + ib * 64));
-                    const int live = kPieces * min(64, nx - ib * 64);
-#pragma unroll
-                    for (int u = 0; u < kPieces; u++)
-                        if (lane + 64 * u < live) row[lane + 64 * u] = out[w][lane + 64 * u];
-                    wave_sync();
-                } else if (in) {
-                    A[p] = a;
+                double dyx = ((double)X[v + 2] - (double)X[v]) * (0.5 * ihy);
+                double dyz = ((double)Z[v + 2] - (double)Z[v]) * (0.5 * ihy);
+                double dzx = ((double)Xh[v] - (double)Xl[v]) * (0.5 * ihz);
+                double dzy = ((double)Yh[v] - (double)Yl[v]) * (0.5 * ihz);
+                double dxz = ((double)Ze[v] - (double)Zw[v]) * (0.5 * ihx);
+                double dxy = ((double)Ye[v] - (double)Yw[v]) * (0.5 * ihx);
+                if (cy || j == 0 || j == ny - 1) {
+                    dyx = dax(bx, p, j, ny, nx, ihy, cy);
+                    dyz = dax(bz, p, j, ny, nx, ihy, cy);
                 }
+                if (!zin) {
+                    dzx = dax(bx, p, k, nz, nxy, ihz, cz);
+                    dzy = dax(by, p, k, nz, nxy, ihz, cz);
+                }
+                if (!xin) {
+                    dxz = dax(bz, p, iq, nx, 1, ihx, cx);
+                    dxy = dax(by, p, iq, nx, 1, ihx, cx);
+                }
+                a.w = (T)(dyz - dzy);
+                c.x = (T)(dzx - dxz);
+                c.y = (T)(dxy - dyx);
+                c.z = (T)0;
+                c.w = (T)0;
+                // the wave's 64 records in memory order (a wave's own rows: no block barrier)
+                V *own = (V *)&out[w][kPieces * lane];
+                own[0] = a;
+                own[1] = c;
+                wave_sync();
+                Piece *row = (Piece *)(A + 2 * ((int64_t)k * nxy + (int64_t)j * nx + ib * 64));
+                const int live = kPieces * min(64, nx - ib * 64);
+#pragma unroll
+                for (int u = 0; u < kPieces; u++)
+                    if (lane + 64 * u < live) row[lane + 64 * u] = out[w][lane + 64 * u];
+                wave_sync();
                 const float fb2 = (float)(dx0 * dx0 + dy0 * dy0 + dz0 * dz0);
                 if (in && fb2 > local) local = fb2;  // NaN compares false and is skipped
             }
@@ -207,24 +223,50 @@ __global__ __launch_bounds__(256) void prep_kernel(const S *__restrict__ bx,
             q += (int64_t)kRows * nx;
         }
     }
-    // block maximum, then one atomic per block (non-negative floats order like ints)
-    for (int off = 32; off > 0; off >>= 1) {
-        const float o = __shfl_xor(local, off);
-        local = o > local ? o : local;
-    }
-    __shared__ float wmax[4];
-    if (lane == 0) wmax[w] = local;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float m = 0.0f;
-        for (int v = 0; v < 4; v++) m = wmax[v] > m ? wmax[v] : m;
-        if (m > 0.0f) {
-            if (m > FLT_MAX) m = FLT_MAX;
-            // (most blocks see a larger maximum there already: thousands of atomics on one
-            // word take longer than the pass)
-            if (m > *(volatile float *)bmax2) atomicMax((int *)bmax2, __float_as_int(m));
+    block_max(local, bmax2);
+}
+
+// Records without twist need no neighbours: the three planes side by side, nodes in memory
+// order whatever the rows are, four of a thread's on their way at once, a block's next to
+// each other. Bound by memory, 12 bytes read and 16 written per FP32 node. By patches and
+// rows as above, where the lanes past the ends of ragged rows wait too, FP32 planes to
+// FP64 records of 65x400x400 nodes took 199 us for 110 here, 129x300x300 155 for 114, 256^3
+// 173 for 163; FP32 records of 256x256x128 42 for 45. (Four nodes a grid apart: 256^3 from
+// FP64 207 us for 188.)
+template <typename S, typename T>
+__global__ __launch_bounds__(256) void pack_kernel(const S *__restrict__ bx, const S *__restrict__ by,
+                                                   const S *__restrict__ bz, int64_t nn,
+                                                   typename V4<T>::t *__restrict__ A,
+                                                   float *__restrict__ bmax2)
+{
+// sums and differences round as written
+#pragma clang fp contract(off)
+    constexpr int64_t step = 256;
+    float local = 0.0f;
+    for (int64_t q = (int64_t)blockIdx.x * kRows * step + threadIdx.x; q < nn;
+         q += (int64_t)gridDim.x * kRows * step) {
+        S X[kRows], Y[kRows], Z[kRows];
+#pragma unroll
+        for (int v = 0; v < kRows; v++) {
+            const int64_t p = q + v * step < nn ? q + v * step : q;
+            X[v] = bx[p], Y[v] = by[p], Z[v] = bz[p];
+        }
+#pragma unroll
+        for (int v = 0; v < kRows; v++) {
+            const int64_t p = q + v * step;
+            if (p >= nn) break;
+            const double x = (double)X[v], y = (double)Y[v], z = (double)Z[v];
+            typename V4<T>::t a;
+            a.x = (T)x;
+            a.y = (T)y;
+            a.z = (T)z;
+            a.w = (T)0;
+            A[p] = a;
+            const float fb2 = (float)(x * x + y * y + z * z);
+            if (fb2 > local) local = fb2;  // NaN compares false and is skipped
         }
     }
+    block_max(local, bmax2);
 }
 
 // Stretched grids: 1 / width of every cell of every axis (a uniform axis repeats
@@ -286,6 +328,15 @@ __global__ void fill_u32_kernel(uint32_t *p, int64_t n, uint32_t v)
 template <typename S, typename T>
 hipError_t run_prep(const fq_field &f, int want_tw, void *A, float *bmax2, hipStream_t s)
 {
+    using V = typename V4<T>::t;
+    const S *const b[3] = {(const S *)f.b[0], (const S *)f.b[1], (const S *)f.b[2]};
+    if (!want_tw) {
+        const int64_t nn = f.n[0] * f.n[1] * f.n[2], need = (nn + 256 * kRows - 1) / (256 * kRows);
+        const unsigned blocks = (unsigned)(need < 4096 ? need : 4096);
+        hipLaunchKernelGGL((pack_kernel<S, T>), dim3(blocks), dim3(256), 0, s, b[0], b[1], b[2], nn, (V *)A,
+                           bmax2);
+        return hipGetLastError();
+    }
     const int64_t tx = (f.n[0] + 63) / 64, tz = (f.n[2] + 3) / 4;
     // rows per block: about 4096 blocks where the grid has them (16 per CU), and no more
     // than 32 rows (the row before the first is read twice)
@@ -296,12 +347,10 @@ hipError_t run_prep(const fq_field &f, int want_tw, void *A, float *bmax2, hipSt
     if (pieces * depth < f.n[1]) depth = pieces > 1 ? (f.n[1] + pieces - 1) / pieces : f.n[1];
     int64_t blocks = tx * tz * ((f.n[1] + depth - 1) / depth);
     blocks = (blocks + 7) / 8 * 8;
-    const auto fn = want_tw ? prep_kernel<S, T, true> : prep_kernel<S, T, false>;
-    hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(256), 0, s,
-                       (const S *)f.b[0], (const S *)f.b[1], (const S *)f.b[2], (int)f.n[0],
-                       (int)f.n[1], (int)f.n[2], 1.0 / f.spacing[0], 1.0 / f.spacing[1],
+    hipLaunchKernelGGL((prep_kernel<S, T>), dim3((unsigned)blocks), dim3(256), 0, s, b[0], b[1], b[2],
+                       (int)f.n[0], (int)f.n[1], (int)f.n[2], 1.0 / f.spacing[0], 1.0 / f.spacing[1],
                        1.0 / f.spacing[2], f.coord[0], f.coord[1], f.coord[2], (int)tx, (int)tz,
-                       (int)depth, (typename V4<T>::t *)A, bmax2);
+                       (int)depth, (V *)A, bmax2);
     return hipGetLastError();
 }
 

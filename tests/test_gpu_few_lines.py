@@ -180,3 +180,28 @@ def test_reverse_of_few_lines(fq, nu, nv, prec):
                 if prec == F64:
                     lim = 1e-12 * np.abs(ref).max()
                     assert np.abs(gb - ref).max() <= lim, (seg, np.abs(gb - ref).max(), lim)
+
+
+@pytest.mark.parametrize("n", [(2, 2, 2), (5, 9, 6), (16, 8, 8), (41, 5, 5), (33, 31, 2), (64, 16, 16), (201, 150, 150)])
+@pytest.mark.parametrize("prec", [F32X, F64], ids=["f32x", "f64"])
+def test_records_without_twist_at_block_edges(fq, n, prec):
+    """Node records without twist (Bx, By, Bz, 0 of every node, in the type the trace
+    computes in) of grids of fewer, exactly and more nodes than a block takes at once, and
+    of more than all blocks do, from FP32 and FP64 fields: exact, read from the workspace."""
+    import torch
+
+    rng = np.random.default_rng(sum(n))
+    for dt in (np.float32, np.float64):
+        B = rng.normal(size=(3, n[2], n[1], n[0])).astype(dt)
+        B[0].flat[3], B[2].flat[-1] = -0.0, np.nan
+        _say(f"records without twist {n}, precision {prec}, {np.dtype(dt)}")
+        r = fq.trace(_dev(B), cubic_grid(*n), torch.zeros((1, 3), dtype=torch.float64).cuda(),
+                     params=fq.Params(precision=prec, want_tw=False, max_steps=50))
+        torch.cuda.synchronize()
+        want = np.zeros((n[0] * n[1] * n[2], 4), dtype=np.float32 if prec == F32X else np.float64)
+        want[:, :3] = B.reshape(3, -1).T
+        ws, bits = to_np(r["_ws"]), want.view(np.uint8).ravel()
+        # (workspace arrays begin at multiples of 256 bytes)
+        at = [o for o in range(0, len(ws) - len(bits) + 1, 256) if ws[o] == bits[0]
+              and np.array_equal(ws[o:o + 64], bits[:64])]
+        assert any(np.array_equal(ws[o:o + len(bits)], bits) for o in at)

@@ -143,3 +143,14 @@ def test_prep_launch_fits_every_grid_that_memory_holds(launches, n, tw):
     assert status == 0 and len(rows) == 1
     grid, threads, _ = rows[0]
     assert threads == 256 and 0 < grid * threads < 1 << 32
+
+
+@pytest.mark.parametrize("dtype,precision", [(0, F32X), (1, F32X), (0, F64), (1, F64)])
+def test_records_without_twist_are_packed_in_memory_order(launches, dtype, precision):
+    """No neighbours, so no march along y with its lanes past the ends of ragged rows."""
+    for n in ((2, 2, 2), (65, 400, 400), (300, 300, 5)):
+        for tw, kernel in ((0, "pack_kernel"), (1, "prep_kernel")):
+            status, rows = launches("prep", *n, dtype, precision, tw)
+            assert status == 0 and len(rows) == 1 and kernel in rows[0][2]
+            if not tw:
+                assert rows[0][0] == min(4096, -(-n[0] * n[1] * n[2] // 1024))
