@@ -154,3 +154,16 @@ def test_records_without_twist_are_packed_in_memory_order(launches, dtype, preci
             assert status == 0 and len(rows) == 1 and kernel in rows[0][2]
             if not tw:
                 assert rows[0][0] == min(4096, -(-n[0] * n[1] * n[2] // 1024))
+
+
+def test_tape_kernels_on_both_sides_of_the_limit(route, launches):
+    """The planes of the adjoint tests on both sides: 270 x 270 on a face and 192 x 192 inside
+    a 24-node grid are traced by the one-lane kernel, what lies inside them by the other."""
+    n = (24, 21, 19)
+    for side, z, few in ((270, 0.0, 0), (192, 0.25, 0), (27, 0.0, 1), (27, 0.25, 1)):
+        for precision in (F32X, F64):
+            assert route("fit", n, (side, side), precision=precision, height=z)["few"] == few
+    for few, kernel in ((0, "trace_kernel"), (1, "trace_quad_kernel")):
+        for precision, store in ((F32X, 0), (F64, 1)):
+            status, rows = launches.trace(precision=precision, store=store, few=few, tape=1)
+            assert status == 0 and [r for r in rows if kernel in r[2]] == rows and len(rows) == 1
