@@ -627,14 +627,15 @@ __global__ void graze_kernel(const TraceJob *__restrict__ jobs, int job, double 
     }
 }
 
-// The kernel for a twist mode, scheme, method and mapping surface.
+// The kernel for a twist mode, scheme, method and mapping surface (positions only: the
+// FP64 re-trace).
 template <typename T, typename S, bool UNI, bool TAPE, int SCH, bool CYL>
 const void *kernel_of_s(int twm)
 {
-    if constexpr (sizeof(T) == 8 && !TAPE)
+    if constexpr (sizeof(T) == 8 && !TAPE) {
         if (twm == 3) return (const void *)trace_kernel<T, S, 3, UNI, TAPE, SCH, false, CYL>;
-    if constexpr (!TAPE)
         if (twm == 2) return (const void *)trace_kernel<T, S, 2, UNI, TAPE, SCH, false, CYL>;
+    }
     return twm == 1 ? (const void *)trace_kernel<T, S, 1, UNI, TAPE, SCH, false, CYL>
                     : (const void *)trace_kernel<T, S, 0, UNI, TAPE, SCH, false, CYL>;
 }
@@ -1067,6 +1068,7 @@ hipError_t launch_trace(int prec, int store, int twm, const TraceJob *jobs_dev,
     if (!f64 && s64) return hipErrorInvalidValue;  // FP32 arithmetic reads FP32 records only
     if (tp.scheme < SCH_RKF45 || tp.scheme > SCH_RK4_38) return hipErrorInvalidValue;
     if (tp.cyl && tp.scheme != SCH_RKF45) return hipErrorInvalidValue;
+    if (twm < 0 || twm > (f64 ? 3 : 1)) return hipErrorInvalidValue;
     const bool one = tp.njobs == 1 && !tp.dynamic_last;
     const void *fn;
     if (tp.tape) {
@@ -1083,7 +1085,6 @@ hipError_t launch_trace(int prec, int store, int twm, const TraceJob *jobs_dev,
     } else {
         if (tp.method == FQ_METHOD_II && (tp.scheme != SCH_RKF45 || tp.cyl || twm == 2 || twm == 3))
             return hipErrorInvalidValue;
-        if (twm == 3 && !f64) return hipErrorInvalidValue;
         fn = kernel_for<false>(f64, s64, one && !tp.stretched && !tp.cyl, twm, tp);
     }
     TraceParams p = tp;

@@ -119,10 +119,6 @@ template <typename T> __host__ __device__ __forceinline__ bool finite_(T x)
 {
     return __builtin_isfinite(x);
 }
-template <typename T> __host__ __device__ __forceinline__ T sel3(int a, T x, T y, T z)
-{
-    return a == 0 ? x : (a == 1 ? y : z);
-}
 
 // P(u,v,w) = c0 + c1 u + c2 v + c3 w + c4 uv + c5 uw + c6 vw + c7 uvw, 7 FMAs.
 template <typename T>

@@ -322,9 +322,10 @@ template <typename T, typename S> const void *pick(int twm, const TraceParams &t
     if (tp.method == FQ_METHOD_II)
         return twm == 1 ? (const void *)trace_quad_kernel<T, S, 1, true, false>
                         : (const void *)trace_quad_kernel<T, S, 0, true, false>;
-    return twm == 1   ? (const void *)trace_quad_kernel<T, S, 1, false, false>
-           : twm == 0 ? (const void *)trace_quad_kernel<T, S, 0, false, false>
-                      : (const void *)trace_quad_kernel<T, S, 2, false, false>;
+    if constexpr (sizeof(T) == 8)
+        if (twm > 1) return (const void *)trace_quad_kernel<T, S, 2, false, false>;
+    return twm == 1 ? (const void *)trace_quad_kernel<T, S, 1, false, false>
+                    : (const void *)trace_quad_kernel<T, S, 0, false, false>;
 }
 
 }  // namespace

@@ -167,3 +167,14 @@ def test_tape_kernels_on_both_sides_of_the_limit(route, launches):
         for precision, store in ((F32X, 0), (F64, 1)):
             status, rows = launches.trace(precision=precision, store=store, few=few, tape=1)
             assert status == 0 and [r for r in rows if kernel in r[2]] == rows and len(rows) == 1
+
+
+def test_positions_only_passes_are_fp64(launches):
+    """An FP32 pass takes no positions-only form, in either kernel."""
+    for few in (0, 1):
+        for twm, ok in ((-1, False), (0, True), (1, True), (2, False), (3, False)):
+            status, rows = launches.trace(precision=F32X, store=0, twm=twm, few=few)
+            assert (status == 0) == ok and bool(rows) == ok, (few, twm)
+        for twm, ok in ((0, True), (1, True), (2, True), (3, True), (4, False)):
+            status, rows = launches.trace(twm=twm, few=few, list_=1)
+            assert (status == 0) == ok and bool(rows) == ok, (few, twm)
