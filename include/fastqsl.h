@@ -124,7 +124,8 @@ typedef struct {
     int32_t precision; /* FQ_PREC_F32X (default) or FQ_PREC_F64 */
     int32_t want_tw;   /* nonzero: integrate Tw (the curl planes are built) */
     int32_t block;     /* threads per block of the tracer: 64, 128, 192 or 256; 0 = 256 */
-    int32_t waves_per_cu; /* resident waves per CU the tracer's grid is sized for; 0 = the most that fit */
+    int32_t waves_per_cu; /* resident waves per CU the tracer's grid is sized for; 0 = the most that fit.
+                             (The adjoint's recording pass keeps its own shape.) */
     double graze;      /* FQ_PREC_F32X only: both halves of a line whose field makes an angle
                           |Bn/B| below this with S0 at its seed, and a half line whose field
                           makes such an angle with the face it ends on (these turn FP32
@@ -162,8 +163,9 @@ typedef struct {
                           long lines) then runs at three waves per SIMD and
                           takes its half lines longest first (waves of short lines end early),
                           so that the other maps' FP32 passes find room beside its waves: more
-                          maps per second in flight, a longer FP64 pass for one map alone.
-                          Results are the same bit for bit; default 0 */
+                          maps per second in flight, a longer FP64 pass for one map alone. In
+                          either precision fewer calls take the tracer form for few lines, which
+                          spreads a call over more of the chip. Results are the same bit for bit; default 0 */
     int32_t reserved2; /* must be 0 */
 } fq_params;
 

@@ -17,7 +17,9 @@
 //                  values of B and curl B of each cell go to the nodes;
 //   grad_planes    adds dL/dB of the nodes and the transpose of the curl
 //                  differences applied to dL/d(curl B) into the caller's planes.
-// All of it is FP64.
+// The map's adjoint, the node sums and the curl's transpose are FP64; the replay and the
+// sweep compute in the type of the forward pass that they replay (FP64, or the FP32 pass of
+// the F32X form). RKF45's in FP64 takes four lanes to a half line (adjoint_quad.hip).
 #include <math.h>
 
 #include "adjoint_dev.h"

@@ -23,9 +23,9 @@
 //    continues in the neighbouring cell, or ends if the face is a box face.
 //  * Persistent lanes and a global queue. Line lengths differ by orders of
 //    magnitude; a lane that finishes pops the next half line from a global counter
-//    (one atomic per wave via a ballot), so waves never idle on their longest line.
-//    Queue items follow 64-seed tiles, so the lanes of a wave start on neighbouring
-//    seeds and read neighbouring cells.
+//    (one atomic per wave via a ballot), so a wave goes on past its longest line (in a
+//    3-D map once all of its lanes are idle, see refill_min). Queue items follow 64-seed
+//    tiles, so the lanes of a wave start on neighbouring seeds and read neighbouring cells.
 // Launches of few lines take four lanes to a half line instead (trace_quad.hip).
 #include "fq_internal.h"
 #include "trace_core.h"
@@ -81,7 +81,7 @@ template <typename T> constexpr int refill_min() { return sizeof(T) == 4 ? 24 : 
 
 // TWM: 0 = no twist (narrow records), 1 = twist, 2 = positions only on wide records
 // (the FP64 re-trace, which keeps the twist of the first pass); 3 = as 2, held to
-// three waves per SIMD (168 VGPRs, 52-64 bytes of spills per lane) for calls
+// three waves per SIMD (168 VGPRs, 28-64 bytes of scratch per lane, 112 with a cylinder) for calls
 // that share the GPU with other maps in flight: its waves then leave room for theirs
 // (lists that four lanes to a line trace run three waves per SIMD in any call).
 // SCH: the integration scheme (Scheme in trace_core.h), the adjoint's forward pass
@@ -89,15 +89,18 @@ template <typename T> constexpr int refill_min() { return sizeof(T) == 4 ? 24 : 
 // end values go to the records' uv array). CYL: jobs may run inside a cylinder.
 //
 // Waves per SIMD each kernel's registers are held to. With the twist summed stage by
-// stage the FP32 kernels need 142-160 VGPRs and the FP64 ones 245-252, without spills:
-// three waves and two (168 and 256). More waves fill the issue slots that a wave leaves
+// stage the FP32 kernels need 138-160 VGPRs and the FP64 ones 243-252, without spills:
+// three waves and two (168 and 256); the cylinder's FP64 one takes 256 and 16 bytes of
+// scratch. More waves fill the issue slots that a wave leaves
 // while it waits for its cell fetches (29% of an FP64 wave's time, 32% of a multi-job
 // FP32 wave's): a 1024 x 1024 FP64 map 7.36 -> 5.57 ms (one wave -> two), a 256x256x128
 // voxel map 195 -> 187 ms and a batch of 8 cubes 35.7 -> 32.8 ms (two -> three; the
 // single-job FP32 kernel had three). Four waves of FP32 (128 VGPRs, spills) are slower
 // than three (4.88 -> 5.00 ms at 1024 x 1024). Method II in FP64 stays at one wave: at
 // two it spills 680 bytes (5.4 -> 6.3 ms); its FP32 kernels (198-203 VGPRs) and the
-// cylinder's (183) run two.
+// cylinder's (183) run two. (Cylinders, against the multi-job kernels that they were a
+// case of, of 128x128x96 nodes: 64 x 32 points in FP64 2.33 -> 1.62 ms; where lines run to
+// max_steps, 1024 x 384 points in FP64 1150 -> 1000 ms, in F32X 2700 -> 2170.)
 template <typename T, int TWM, bool M2, bool CYL> constexpr int waves_per_simd()
 {
     if (sizeof(T) == 4) return M2 || CYL ? 2 : 3;
@@ -1100,7 +1103,9 @@ hipError_t launch_trace(int prec, int store, int twm, const TraceJob *jobs_dev,
             // 1024 x 1024 plane and of a cut would go the other way, 4530 and 1396 us for
             // 4457 and 1224; 524288 the same within noise; without end a voxel map's trace
             // 178.0 ms for 175.0). The half lines still on their way at the end of the FP32
-            // pass are few by nature.
+            // pass are few by nature and go with four lanes at any length: a limit would cost
+            // every F32X call one more launch, 4 us, for calls whose max_steps ends most of
+            // their lines (700 x 700 points, 20 steps: 1.53 ms, 1.22 with one lane).
             const hipError_t e = launch_trace_quad(f64, s64, twm, jobs_dev, tp, counter,
                                                    tp.list_rev ? INT64_MAX : kFewList, ncu, block, waves_per_cu, s);
             if (e != hipSuccess || tp.list_rev) return e;

@@ -1,15 +1,15 @@
 // Tracer with four lanes to a half line, for launches of few lines: RKF45, Method I and
-// II, the adjoint's forward pass, uniform and stretched grids, any number of jobs (trace.hip has the queue, the
-// records and everything else that the two kernels share in meaning; trace_quad.h the
-// step). Results are those of trace_kernel, bit for bit.
+// II, the adjoint's forward pass, uniform and stretched grids, any number of jobs
+// (trace.hip has the queue, the records and everything else that the two kernels share in
+// meaning; trace_quad.h the step). Results are those of trace_kernel, bit for bit.
 //
 // Bound by the latency of the longest line's trial steps, one after the other: a step is
 // about 60 % of the one-lane step's instructions in a row, because each lane evaluates
 // one component of the field and its curl instead of three, and a cell's records are
-// fetched by three lanes, one component each. Against one lane to a line, whole calls: a 32^3
-// look of 16384 lines 1097 -> 761 us, a 128^3 FP64 plane 812 -> 676, an interior cut of
-// 255 x 129 points 1612 -> 1224, 30001 seeds from a list 3352 -> 2895; through the FP64
-// re-trace of an FP32 pass also large calls, a 1024 x 1024 plane 4951 -> 4457, eight in a
+// fetched by three lanes, one component each. Against one lane to a line, whole calls: a
+// 32 x 32 plane of 64^3 nodes 1097 -> 761 us, a 128 x 128 one in FP64 812 -> 676 (both
+// without a tile order), an interior cut of 157 x 211 points 1612 -> 1224, 30001 seeds from
+// a list 3352 -> 2895; through the FP64 re-trace of an FP32 pass also large calls, a 1024 x 1024 plane 4951 -> 4457, eight in a
 // batch 32.7 -> 27.1 ms; the map, loss and gradient of a 256 x 256 plane, whose forward
 // pass this is as well, 6.26 -> 6.12 ms.
 #include "fq_internal.h"

@@ -62,15 +62,15 @@ def launches(tmp_path_factory):
     return call
 
 
-@pytest.mark.parametrize("kind,height", [("fit", 0.0), ("fit", 0.13), ("fit3", 0.0)])
-@pytest.mark.parametrize("precision,scheme", [(F32X, RKF45), (F32X, RK4), (F64, RKF45), (F64, RK4), (F64, RK4_38)])
+# (fixed steps differentiate planes on a face only)
+@pytest.mark.parametrize("kind,height,precision,scheme",
+                         [("fit", 0.0, p, s) for p in (F32X, F64) for s in (RKF45, RK4, RK4_38)]
+                         + [(k, z, p, RKF45) for k, z in (("fit", 0.13), ("fit3", 0.0)) for p in (F32X, F64)])
 def test_gradient_layout_follows_the_reverse_kernel(route, kind, height, precision, scheme):
     """Node gradients lie side by side only for the reverse kernel whose half lines have a
     lane per component (FP64, RKF45); with one lane to a half line each component has a
     plane of its own, where neighbouring lines' additions share cache lines."""
     n = (40, 36, 30)
-    if scheme != RKF45 and (kind == "fit3" or height):
-        pytest.skip("fixed steps differentiate planes on a face only")
     r = route(kind, n, (12, 11, 5), precision=precision, scheme=scheme, height=height)
     if precision == F64 and scheme == RKF45:
         assert (r["node_step"], r["value_step"], r["grad_form"]) == (6, 1, 1)
