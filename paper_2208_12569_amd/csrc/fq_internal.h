@@ -136,7 +136,7 @@ struct TraceParams {
     const FixEntry *list;          // list mode: trace exactly these half lines
     const uint32_t *list_count;
     int64_t list_cap;
-    int32_t list_rev;              // list mode: entry k sits at list[list_cap - 1 - k]
+    int32_t list_rev;              // list mode, one lane: entry k sits at list[list_cap - 1 - k]
     int32_t scheme;                // integration scheme (FQ_SCHEME_*)
     int32_t method;                // FQ_METHOD_I or FQ_METHOD_II (tangent vectors carried)
     int32_t stretched;             // some job's grid is stretched (multi-job kernels then)

@@ -419,7 +419,6 @@ __global__ __launch_bounds__(256, (waves_per_simd<T, TWM, M2, CYL>())) void trac
 
         // ---- one trial step -------------------------------------------------------------
         if (jb >= 0 && fin_st < 0) {
-            n_trial++;
             const unsigned acc_before = n_acc;
             if (CYLK && cylj) {
                 sv_c0 = L.c0, sv_c1 = L.c1, sv_c2 = L.c2;
@@ -535,6 +534,7 @@ __global__ __launch_bounds__(256, (waves_per_simd<T, TWM, M2, CYL>())) void trac
             }
             jb = -1;
             need_load = false;
+            n_trial += L.trials;
             n_half++;
         }
 
@@ -1097,18 +1097,17 @@ hipError_t launch_trace(int prec, int store, int twm, const TraceJob *jobs_dev,
             if (tp.few)
                 return launch_trace_quad(f64, s64, twm, jobs_dev, tp, counter, INT64_MAX, ncu, block,
                                          waves_per_cu, s);
-        } else {
-            // Re-trace lists, whose lengths are on the device: one of the two kernels finds
+        } else if (!tp.list_rev) {
+            // The re-trace list, whose length is on the device: one of the two kernels finds
             // nothing to do. Up to kFewList halves four lanes to a line (65536: the list of a
             // 1024 x 1024 plane and of a cut would go the other way, 4530 and 1396 us for
             // 4457 and 1224; 524288 the same within noise; without end a voxel map's trace
-            // 178.0 ms for 175.0). The half lines still on their way at the end of the FP32
-            // pass are few by nature and go with four lanes at any length: a limit would cost
-            // every F32X call one more launch, 4 us, for calls whose max_steps ends most of
-            // their lines (700 x 700 points, 20 steps: 1.53 ms, 1.22 with one lane).
-            const hipError_t e = launch_trace_quad(f64, s64, twm, jobs_dev, tp, counter,
-                                                   tp.list_rev ? INT64_MAX : kFewList, ncu, block, waves_per_cu, s);
-            if (e != hipSuccess || tp.list_rev) return e;
+            // 178.0 ms for 175.0). The list of half lines that the FP32 pass could not finish
+            // goes with one lane: usually none, else lines that never end, or many (700 x 700
+            // points of 20 steps each 1.53 -> 1.22 ms).
+            const hipError_t e = launch_trace_quad(f64, s64, twm, jobs_dev, tp, counter, kFewList, ncu, block,
+                                                   waves_per_cu, s);
+            if (e != hipSuccess) return e;
             p.least = kFewList;
         }
     }

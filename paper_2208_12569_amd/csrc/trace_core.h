@@ -653,6 +653,7 @@ __host__ __device__ __forceinline__ void lane_iterate(Lane<T> &L, const T cb[3][
         const T g2 = mn(land ? mx(g1, L.h) : g1, T(4));
         hn = acc ? (land & !(grow >= 1.0f) ? g1 : g2) : hn;
     }
+    const bool again = (hn == L.h) & (force == L.force);
     if (!cross) {
         L.h = hn;
         L.force = force;
@@ -701,6 +702,12 @@ __host__ __device__ __forceinline__ void lane_iterate(Lane<T> &L, const T cb[3][
     L.c2 += (a2 & on) ? (u2 ? 1 : -1) : 0;
     need_load = need_load | moved | on;
     const bool dead = !live | (step & (null_in | (broke & !land)));
+    // A trial that moves nothing and asks for the step it had (the smallest one, rejected)
+    // will be the same trial for good: the line's other trials are taken as done. (A layer
+    // of zero field under 700 x 700 points holds 28 000 such half lines, max_steps trials
+    // each: 1.42 -> 0.58 s. Not in the step with four lanes to a half line, whose longest
+    // chain the test would cost 3%.)
+    if (!FIXED && (again & !(dead | cross | acc))) L.trials = K.max_steps;
     if (dead | at_box) {
         fin_st = at_box ? 0
                  : over ? kMaxSteps

@@ -109,7 +109,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? (M2 ? 3 : 4) : (M2 ? 2 : 3)) 
                     LineAt at;
                     bool forward;
                     if (tp.list) {
-                        const FixEntry e = gptr(tp.list)[tp.list_rev ? tp.list_cap - 1 - it : it];
+                        const FixEntry e = gptr(tp.list)[it];
                         j = e.job;
                         at = line_at(jobs[j], e.line);
                         forward = e.half != 0;
@@ -324,8 +324,9 @@ template <typename T, typename S> const void *pick(int twm, const TraceParams &t
                         : (const void *)trace_quad_kernel<T, S, 0, true, false>;
     if constexpr (sizeof(T) == 8)
         if (twm > 1) return (const void *)trace_quad_kernel<T, S, 2, false, false>;
-    return twm == 1 ? (const void *)trace_quad_kernel<T, S, 1, false, false>
-                    : (const void *)trace_quad_kernel<T, S, 0, false, false>;
+    if constexpr (sizeof(T) == sizeof(S))
+        if (twm == 1) return (const void *)trace_quad_kernel<T, S, 1, false, false>;
+    return twm == 0 ? (const void *)trace_quad_kernel<T, S, 0, false, false> : nullptr;
 }
 
 }  // namespace
@@ -336,6 +337,7 @@ hipError_t launch_trace_quad(bool f64, bool s64, int twm, const TraceJob *jobs_d
 {
     const void *fn = !f64 ? pick<float, float>(twm, tp)
                      : s64 ? pick<double, double>(twm, tp) : pick<double, float>(twm, tp);
+    if (!fn || tp.list_rev) return hipErrorInvalidValue;
     const int per_cu = tracer_blocks_per_cu(fn, block, waves_per_cu);
     TraceParams p = tp;
     void *args[4] = {&jobs_dev, &p, &counter, &most};

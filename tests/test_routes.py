@@ -178,3 +178,25 @@ def test_positions_only_passes_are_fp64(launches):
         for twm, ok in ((0, True), (1, True), (2, True), (3, True), (4, False)):
             status, rows = launches.trace(twm=twm, few=few, list_=1)
             assert (status == 0) == ok and bool(rows) == ok, (few, twm)
+
+
+def test_unfinished_half_lines_take_one_lane(launches):
+    """The re-trace list goes to both kernels, one of which finds nothing to do; the list of
+    half lines that the FP32 pass could not finish to the one-lane kernel alone, which
+    ends a line whose trials repeat."""
+    for store in (0, 1):
+        status, rows = launches.trace(store=store, list_=1, twm=2)
+        assert status == 0 and ["trace_quad_kernel" in r[2] for r in rows] == [True, False]
+        status, rows = launches.trace(store=store, list_=1, rev=1)
+        assert status == 0 and len(rows) == 1 and "trace_quad_kernel" not in rows[0][2]
+
+
+def test_a_trial_that_repeats_ends_the_line(tmp_path):
+    """The one-lane trial step on the host: a rejected step of the smallest length leaves
+    every trial after it the same, so the line ends with all of its trials counted."""
+    exe = str(tmp_path / "step_driver")
+    subprocess.check_call([*GPP, "-O2", "-ffp-contract=off", "-w",
+                           os.path.join(ROOT, "tests", "sanitize", "step_driver.cpp"), "-o", exe])
+    for line in subprocess.run([exe], capture_output=True, text=True, check=True).stdout.splitlines():
+        name, out_of_trials, stood_still, _, faults = line.split()
+        assert int(out_of_trials) >= int(stood_still) > 100 and int(faults) == 0, line
