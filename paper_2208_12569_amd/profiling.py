@@ -10,6 +10,7 @@ the same process.
         "<command>" [kernel] [kernel ms]
   python -m paper_2208_12569_amd.profiling valu <SQ pass A csv> <SQ pass B csv> <out.md>
         "<command A>" "<command B>" <kernel ms> <trial steps> <cell fetches>
+  python -m paper_2208_12569_amd.profiling waits <SQ pass csv> <out.md> "<command>"
 """
 
 from __future__ import annotations
@@ -172,6 +173,35 @@ def valu_md(a_csv: str, b_csv: str, command_a: str, command_b: str, kernel_ms: f
     return "\n".join(rows) + "\n"
 
 
+WAITS = ("SQ_WAVES", "SQ_WAVE_CYCLES", "SQ_WAIT_ANY", "SQ_WAIT_INST_ANY", "SQ_ACTIVE_INST_ANY",
+         "SQ_INSTS_VALU", "SQ_ACTIVE_INST_VALU", "SQ_THREAD_CYCLES_VALU")
+
+
+def waits_md(path: str, command: str, rows: int = 20) -> str:
+    """What the waves of each of the library's kernels do with their time, from one SQ counter pass: issue
+    instructions, wait for an issue slot that other waves hold, or wait for something else
+    (their own loads and results)."""
+    tot = {}
+    for c in WAITS:
+        for name, v in _counter_rows(path, c):
+            k = tot.setdefault(name, dict.fromkeys(WAITS, 0.0) | {"n": 0})
+            k[c] += v
+            k["n"] += c == WAITS[0]
+    out = [f"Command: `{command}`", "",
+           "Shares of the waves' resident time; kernels with the most of it first.", "",
+           "| kernel | launches | waves a launch | VALU instructions a wave | lanes per VALU instruction "
+           "| issuing | waiting for an issue slot | waiting for data |", "|---|---|---|---|---|---|---|---|"]
+    own = [k for k in tot if "fq::" in k]
+    for name in sorted(own, key=lambda k: -tot[k]["SQ_WAVE_CYCLES"])[:rows]:
+        k = tot[name]
+        w, cyc = max(k["SQ_WAVES"], 1.0), max(k["SQ_WAVE_CYCLES"], 1.0)
+        out.append(f"| {_short(name).split('(')[0]} | {k['n']} | {w / k['n']:.0f} | {k['SQ_INSTS_VALU'] / w:.0f} | "
+                   f"{k['SQ_THREAD_CYCLES_VALU'] / max(k['SQ_ACTIVE_INST_VALU'], 1.0):.1f} | "
+                   f"{k['SQ_ACTIVE_INST_ANY'] / cyc:.2f} | {k['SQ_WAIT_INST_ANY'] / cyc:.2f} | "
+                   f"{k['SQ_WAIT_ANY'] / cyc:.2f} |")
+    return "\n".join(out) + "\n"
+
+
 def main(argv):
     if argv[0] == "stats":
         open(argv[2], "w").write(stats_md(argv[1], argv[3]))
@@ -190,6 +220,8 @@ def main(argv):
     elif argv[0] == "valu":
         open(argv[3], "w").write(valu_md(argv[1], argv[2], argv[4], argv[5], float(argv[6]),
                                          float(argv[7]), float(argv[8])))
+    elif argv[0] == "waits":
+        open(argv[2], "w").write(waits_md(argv[1], argv[3]))
     else:
         raise SystemExit(__doc__)
 
